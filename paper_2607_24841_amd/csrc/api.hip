@@ -326,16 +326,9 @@ nmdlm_status nmdlm_bbm_attn(const uint64_t* q, const uint64_t* k_cache, const ui
       return NMDLM_ERR_WORKSPACE;
     a = static_cast<int32_t*>(ws);
   }
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  if (!a_out) {
-    // spikes only: one kernel with the IF fused in, when its LDS fits
-    const nmdlm_status rf = launch_attn_if(q, k_cache, vt_cache, cache_cap, T, M, C, H, dh,
-                                           lut_att, theta_a, s_out, nullptr, st);
-    if (rf != NMDLM_ERR_UNSUPPORTED) return rf;
-  }
-  nmdlm_status rc = launch_attn(q, k_cache, vt_cache, cache_cap, T, M, C, H, dh, lut_att, a, st);
-  if (rc != NMDLM_OK || !s_out) return rc;
-  return launch_if(a, T, M, H * dh, theta_a, nullptr, nullptr, nullptr, s_out, st);
+  const AttnCall c{q, k_cache, vt_cache, cache_cap, T, M, C, H, dh, 1, 0, lut_att, theta_a, a_out,
+                   a, s_out, nullptr, false};
+  return launch_attention(c, static_cast<hipStream_t>(stream));
 }
 
 size_t nmdlm_block_step_workspace_size(const nmdlm_model* model, int M, unsigned flags) {

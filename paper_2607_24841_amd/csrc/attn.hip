@@ -5,23 +5,15 @@
 //   num[i,c] = sum_j p_ij V[j,c];  den[i] = sum_j p_ij
 //   a[i,c] = floor(256 * num / den)   (0 if den = 0)
 //
-// The weighted sum runs on v_mfma_i32_16x16x64_i8: the A operand holds
-// p - 128 (signed byte), the B operand the value bits expanded to bytes, and
-// 128 * (number of ones of V[.,c]) is added back, so the int32 result is exact.
+// Both products run on v_mfma_i32_16x16x64_i8, exact in int32: the scores as
+// a 0/1-byte product of key and query bits over the head's channels, the
+// weighted sum with p - 128 (signed byte) against the value bits expanded to
+// bytes, to which 128 * (number of ones of V[.,c]) is added back.
+#include <algorithm>
+
 #include "common.h"
 
 namespace nmdlm {
-
-__device__ __forceinline__ uint32_t expand4_a(uint32_t nib) {
-  return (nib * 0x00204081u) & 0x01010101u;
-}
-
-// Table bytes 4*lane .. 4*lane+3 as one dword (byte loads: any alignment).
-__device__ __forceinline__ int lut_dword(const uint8_t* __restrict__ lut, int lane) {
-  const uint8_t* b = lut + 4 * lane;
-  return (int)((uint32_t)b[0] | ((uint32_t)b[1] << 8) | ((uint32_t)b[2] << 16) |
-               ((uint32_t)b[3] << 24));
-}
 
 // floor(256 * num / den) for 0 <= num <= den (0 when den = 0).  For fewer
 // than 65536 keys, a = 256 num < 2^32 and den < 2^24: the quotient (at most
@@ -35,7 +27,7 @@ __device__ __forceinline__ int32_t attn_norm(long long num, long long den, bool 
   if (small) {
     const uint32_t a = 256u * (uint32_t)num, b = (uint32_t)den;
     uint32_t q = (uint32_t)((float)a * __builtin_amdgcn_rcpf((float)b));
-    const int32_t r = (int32_t)(a - q * b);
+    const int32_t r = (int32_t)(a - __umul24(q, b));
     if (r < 0) --q;
     else if ((uint32_t)r >= b) ++q;
     return (int32_t)q;
@@ -43,13 +35,338 @@ __device__ __forceinline__ int32_t attn_norm(long long num, long long den, bool 
   return (int32_t)((256LL * num) / den);
 }
 
+// The same for four numerators over one denominator, fewer than 65536 keys
+// (0 <= num <= den < 2^24): k = 256 / den, lowered by 2^-20 of itself, more
+// than the rounding errors of the reciprocal and the two products (4 units of
+// 2^-24), so the truncated estimate is the floor or one below it; the
+// remainder 256 num - q den, one rounding of an exact value, decides which.
+// An empty denominator (num = 0) counts as one.
+__device__ __forceinline__ v4i attn_norm4(v4i num, int den_i) {
+  const float den = (float)max(den_i, 1);
+  const float k = __builtin_amdgcn_rcpf(den) * (256.0f - 0x1p-12f);
+  v4i a;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float n = (float)num[e];
+    const float q = __builtin_truncf(n * k);
+    a[e] = (int)q + (__builtin_fmaf(-q, den, 256.0f * n) >= den ? 1 : 0);
+  }
+  return a;
+}
+
+// ---------------------------------------------------------------------------
+// One wave's share of the attention of 16*QG queries of one head and
+// timestep: 64-key chunks, each lane (g = lane/16, c = lane%16).
+//
+// Scores: the A operand of tile u (u = 0..3) holds 16 keys, row r = key
+// 16*(r/4) + 4u + r%4 of the chunk, the B operand the 16 queries; the result
+// of lane (g, c) is then the scores of query c with keys 16g + 4u + e, so over
+// the four tiles a lane owns the 16 consecutive keys 16g .. 16g+15 of its
+// query: the operand the weighted sum wants, with no exchange.  A lane's key
+// bits (dh = 128: dword g of the row, two k-steps; dh = 64: 16-bit piece g)
+// become bytes in place as bits & (0x01010101 << i), of value 2^i; the query's
+// byte is 2^(3-i), so a score arrives times 8, the byte offset into the table.
+// The order of the channels differs from the memory order, the same way for
+// keys and queries.
+//
+// Weights: the table sits in LDS four times, the entry p - 128 shifted to byte
+// 0..3 of a dword, so a P operand dword is four reads and two ORs; scores less
+// than 32 apart fall in different banks, equal scores broadcast.
+//
+// Weighted sum: A = the value bits of 16 channels (rows), B = P (columns =
+// queries): lane (g, c) accumulates query c, channels 16n + 4g + e.  Value
+// bits h (16 keys of a channel) become bytes as (x >> i) & 0x01010101 of
+// x = h | h << 12: byte b of dword i is key i + {0, 8, 4, 12}[b], and P is
+// packed to match.
+//
+// Per 32 queries and chunk (QG = 2, dh = 128) that is 125 vector instructions
+// and 32 MFMAs, where scoring by popcounts took 350 vector instructions per 16
+// queries; the key and value expansions (100 of the 125) are shared by the QG
+// query groups.  Bound by LDS (140 clocks of a CU per chunk, 64 of them the 32
+// table reads) and by instruction issue (620 clocks of a SIMD), about equally.
+// T = 4, 16 heads of 128, 2048 queries x 2048 keys: 213 -> 76 us (1.8 POP/s).
+// ---------------------------------------------------------------------------
+typedef uint32_t __attribute__((may_alias)) u32_alias;
+typedef uint16_t __attribute__((may_alias)) u16_alias;
+typedef int __attribute__((may_alias)) i32_alias;
+typedef v4i __attribute__((may_alias)) v4i_alias;
+constexpr uint32_t kByteOnes = 0x01010101u;
+constexpr int kAttnStages = 3;    // chunks of a wave in LDS
+constexpr int kLutEntries = 132;  // scores 0..128, padded to a multiple of four
+
+// Entry s of the table, 8 bytes (a score arrives times 8, as a byte offset):
+// the byte lut[s] - 128 at byte positions 2h and 2h + 1 of two dwords, h = 0, 1
+// the half of the table.
+struct AttnLut {
+  int e[2][kLutEntries][2];
+};
+__device__ __forceinline__ void fill_lut(AttnLut& sLut, const uint8_t* __restrict__ lut, int tid,
+                                         int nth) {
+  for (int i = tid; i < kLutEntries; i += nth) {
+    const uint32_t v = (uint32_t)lut[i] ^ 0x80u;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) sLut.e[b >> 1][i][b & 1] = (int)(v << (8 * b));
+  }
+}
+
+__device__ __forceinline__ v4i bytes16(uint32_t x) {  // (x >> i) & ones, i = 0..3
+  return v4i{(int)(x & kByteOnes), (int)((x >> 1) & kByteOnes), (int)((x >> 2) & kByteOnes),
+             (int)((x >> 3) & kByteOnes)};
+}
+// key bits in place (values 2^i) and the query bits that make every product 8
+__device__ __forceinline__ v4i key_bytes(uint32_t x) {
+  return v4i{(int)(x & kByteOnes), (int)(x & (kByteOnes << 1)), (int)(x & (kByteOnes << 2)),
+             (int)(x & (kByteOnes << 3))};
+}
+__device__ __forceinline__ v4i query_bytes(uint32_t x) {
+  const v4i b = bytes16(x);
+  return v4i{b[0] << 3, b[1] << 2, b[2] << 1, b[3]};
+}
+
+// A wave's LDS buffer for the chunk being scored: its 64 key rows, in the
+// order the tiles take them, and one value word per channel.
+template <int DHW>
+struct AttnStage {
+  uint64_t k[64 * DHW];
+  uint64_t v[DHW * 64];
+};
+
+// What a lane loads of a chunk: key row `lane`, the value words of channels
+// lane and lane + 64 (whole rows and words: adjacent lanes at adjacent
+// addresses, where fetching the operand pieces directly cost 400 cache
+// accesses per chunk and set the kernel's time).
+template <int DHW>
+struct AttnChunk {
+  uint64_t k[DHW], v[DHW];
+};
+
+template <int DHW, int QG>
+struct AttnWave {
+  static constexpr int NT = DHW * 4;
+  v4i q[QG][DHW];
+  v4i acc[QG][NT];
+  int den[QG];  // sum of p - 128 of query c over this lane's keys
+  int cnt[NT];  // ones of channel 16n + c over this lane's keys
+
+  // query rows r0 + 16u + c (clamped to the last valid row), channels of head h
+  __device__ __forceinline__ void init(const uint64_t* __restrict__ qrow, int dw, int iq0, int mlast,
+                                       int g, int c) {
+#pragma unroll
+    for (int u = 0; u < QG; ++u) {
+      const uint64_t* p = qrow + (size_t)min(iq0 + 16 * u + c, mlast) * dw;
+      if constexpr (DHW == 2) {
+        const uint32_t w = reinterpret_cast<const u32_alias*>(p)[g];
+        q[u][0] = query_bytes(w);
+        q[u][1] = query_bytes(w >> 4);
+      } else {
+        const uint32_t w = reinterpret_cast<const u16_alias*>(p)[g];
+        q[u][0] = query_bytes(w | (w << 12));
+      }
+      den[u] = 0;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) acc[u][n] = v4i{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int n = 0; n < NT; ++n) cnt[n] = 0;
+  }
+
+  // kb: key row 0 of the timestep at this head's words; vb: value word 0 of
+  // the timestep at this head's channels.  The cache capacity is a multiple
+  // of 64, so every row of a chunk holds memory (rows past C+M are masked).
+  __device__ __forceinline__ static void load(AttnChunk<DHW>& ch, const uint64_t* __restrict__ kb,
+                                              const uint64_t* __restrict__ vb, int dw, int d, int jc,
+                                              int lane) {
+    const uint64_t* kr = kb + (size_t)jc * 64 * dw;
+    const uint64_t* vr = vb + (size_t)jc * d;
+#pragma unroll
+    for (int w = 0; w < DHW; ++w) {
+      ch.k[w] = kr[(uint32_t)(lane * dw + w)];
+      ch.v[w] = vr[(uint32_t)(w * 64 + lane)];
+    }
+  }
+
+  // the chunk into LDS
+  __device__ __forceinline__ static void put(const AttnChunk<DHW>& ch, AttnStage<DHW>& st, int lane) {
+    const int slot = ((lane >> 2) & 3) * 16 + (lane >> 4) * 4 + (lane & 3);
+#pragma unroll
+    for (int w = 0; w < DHW; ++w) {
+      st.k[slot * DHW + w] = ch.k[w];
+      st.v[w * 64 + lane] = ch.v[w];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+
+  // tile u's key is row c of the tile, its bits dword g of the row (dh = 128)
+  // or 16-bit piece g (dh = 64)
+  __device__ __forceinline__ static void key_pieces(const AttnStage<DHW>& st, uint32_t (&k)[4], int g,
+                                                    int c) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if constexpr (DHW == 2) k[u] = reinterpret_cast<const u32_alias*>(st.k)[(u * 16 + c) * 4 + g];
+      else k[u] = reinterpret_cast<const u16_alias*>(st.k)[(u * 16 + c) * 4 + g];
+    }
+  }
+  // the bits of channel 16n + c over keys 16g .. 16g+15
+  __device__ __forceinline__ static void value_pieces(const AttnStage<DHW>& st, uint32_t (&v)[NT], int g,
+                                                      int c) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n) v[n] = reinterpret_cast<const u16_alias*>(st.v)[(n * 16 + c) * 4 + g];
+  }
+
+  // 8 * scores of the chunk's keys
+  __device__ __forceinline__ void scores(const uint32_t (&k)[4], v4i (&s)[QG][4]) const {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      v4i k0, k1;
+      if constexpr (DHW == 2) {
+        k0 = key_bytes(k[u]);
+        k1 = key_bytes(k[u] >> 4);
+      } else {
+        k0 = key_bytes(k[u] | (k[u] << 12));
+      }
+#pragma unroll
+      for (int w = 0; w < QG; ++w)
+        s[w][u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(k0, q[w][0], v4i{0, 0, 0, 0}, 0, 0, 0);
+      if constexpr (DHW == 2) {
+#pragma unroll
+        for (int w = 0; w < QG; ++w)
+          s[w][u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(k1, q[w][1], s[w][u], 0, 0, 0);
+      }
+    }
+  }
+
+  // table bytes in place of the scores (tile u's at byte {0, 2, 1, 3}[u])
+  __device__ __forceinline__ static void lookup(v4i (&s)[QG][4], const char* lb) {
+#pragma unroll
+    for (int w = 0; w < QG; ++w)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int b = u == 1 ? 2 : (u == 2 ? 1 : u);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          s[w][u][e] = *reinterpret_cast<const int*>(lb + kLutEntries * 8 * (b >> 1) + 4 * (b & 1) + s[w][u][e]);
+      }
+  }
+
+  __device__ __forceinline__ static void pack(const v4i (&s)[QG][4], v4i (&p)[QG]) {
+#pragma unroll
+    for (int w = 0; w < QG; ++w) p[w] = s[w][0] | s[w][1] | s[w][2] | s[w][3];
+  }
+
+  __device__ __forceinline__ void weigh(const uint32_t (&v)[NT], const v4i (&p)[QG]) {
+#pragma unroll
+    for (int w = 0; w < QG; ++w)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        den[w] = __builtin_amdgcn_sdot4(p[w][i], (int)kByteOnes, den[w], false);
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const uint32_t h = v[n];
+      cnt[n] += __popc(h);
+      const v4i va = bytes16(h | (h << 12));
+#pragma unroll
+      for (int w = 0; w < QG; ++w)
+        acc[w][n] = __builtin_amdgcn_mfma_i32_16x16x64_i8(va, p[w], acc[w][n], 0, 0, 0);
+    }
+  }
+
+  // the chunks jc0, jc0 + step, ... < nch (jc0 < nch).  Two chunks are in
+  // work: while the weighted sum of one runs, the table reads of the next are
+  // in flight, and the loads of the one after that.  Only the last chunk of
+  // the context can be partial.
+  __device__ __forceinline__ void run(const uint64_t* __restrict__ kb, const uint64_t* __restrict__ vb,
+                                      int dw, int d, int J, int nch, int jc0, int step,
+                                      const AttnLut& sLut, AttnStage<DHW>* st, int lane,
+                                      int g, int c, const AttnChunk<DHW>& first) {
+    const char* lb = reinterpret_cast<const char*>(&sLut);
+    AttnChunk<DHW> nxt;
+    int jc = jc0;
+    AttnStage<DHW>*s0 = st, *s1 = st + 1, *s2 = st + 2;  // chunks j - 1, j, j + 1
+    load(nxt, kb, vb, dw, d, min(jc + step, nch - 1), lane);
+    v4i s[QG][4], p[QG];
+    uint32_t k[4], v[NT];
+    put(first, *s0, lane);
+    key_pieces(*s0, k, g, c);
+    put(nxt, *s1, lane);
+    load(nxt, kb, vb, dw, d, min(jc + 2 * step, nch - 1), lane);
+    scores(k, s);
+    lookup(s, lb);
+    key_pieces(*s1, k, g, c);
+    pack(s, p);
+    for (jc += step; jc < nch; jc += step) {
+      value_pieces(*s0, v, g, c);
+      scores(k, s);
+      __builtin_amdgcn_sched_barrier(0);
+      lookup(s, lb);
+      put(nxt, *s2, lane);
+      load(nxt, kb, vb, dw, d, min(jc + 2 * step, nch - 1), lane);
+      key_pieces(*s2, k, g, c);
+      weigh(v, p);
+      __builtin_amdgcn_sched_barrier(0);
+      pack(s, p);
+      AttnStage<DHW>* const t = s0;
+      s0 = s1;
+      s1 = s2;
+      s2 = t;
+    }
+    value_pieces(*s0, v, g, c);
+    const int jl = jc - step;
+    if (jl * 64 + 64 > J) {  // wave-uniform
+      const int nvalid = J - (jl * 64 + 16 * g);  // of this lane's 16 keys
+      const uint32_t vm = nvalid >= 16 ? 0xFFFFu : (nvalid <= 0 ? 0u : ((1u << nvalid) - 1u));
+      const v4i m = bytes16(vm | (vm << 12)) * 0xFF;
+#pragma unroll
+      for (int w = 0; w < QG; ++w) p[w] &= m;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) v[n] &= vm;
+    }
+    weigh(v, p);
+#pragma unroll
+    for (int w = 0; w < QG; ++w) {  // over the four lane groups
+      den[w] += __shfl_xor(den[w], 16);
+      den[w] += __shfl_xor(den[w], 32);
+    }
+    // 128 * the ones of each channel over the wave's keys, added to the sums
+    // of channels 16n + 4g + e (the counts change lanes through the stage)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) cnt[n] += __shfl_xor(cnt[n], 16);
+#pragma unroll
+    for (int n = 0; n < NT; ++n) cnt[n] += __shfl_xor(cnt[n], 32);
+    char* sc = reinterpret_cast<char*>(st);
+#pragma unroll
+    for (int n = 0; n < NT; ++n)  // the four lane groups store the same values
+      *reinterpret_cast<i32_alias*>(sc + 64 * n + 4 * c) = 128 * cnt[n];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const v4i x = *reinterpret_cast<const v4i_alias*>(sc + 64 * n + 16 * g);
+#pragma unroll
+      for (int w = 0; w < QG; ++w) acc[w][n] += x;
+    }
+  }
+};
+
+// valid keys of the chunks jc0, jc0 + step, ... < nch
+__device__ __forceinline__ int keys_of(int jc0, int step, int nch, int J) {
+  if (jc0 >= nch) return 0;
+  const int n = (nch - 1 - jc0) / step + 1;
+  return n * 64 - (((nch - 1 - jc0) % step == 0) ? nch * 64 - J : 0);
+}
+
+// ---------------------------------------------------------------------------
+// k_attn: scores and weighted sums of one (head, 16 queries, timestep), the
+// chunks shared by NW waves whose sums meet in LDS; the IF of the output
+// follows in its own kernel.  For grids too small for one wave per 16 queries
+// (the denoising step's): every load of a short context is in flight at once.
+//
 // grid (H, n_seq * ceil(M/16), T), M queries per sequence, rows of q and
 // a_out sequence-major (n_seq * M per timestep), the caches of sequence s at
-// s * seq_words words past kc / vt; wave i takes 64-key chunks i, i+NW, ...  Every
-// load of a chunk (16 keys per lane, NT value words) is issued before it is
-// scored; with up to 64*NW keys each wave has one chunk, so all the key and
-// value loads of the workgroup are in flight together.  The table is read
-// with ds_bpermute from lut_dw (entry s sits in byte s%4 of lane s/4).
+// s * seq_words words past kc / vt.
+// ---------------------------------------------------------------------------
 template <int DHW, int NW>
 __global__ __launch_bounds__(NW * 64) void k_attn(const uint64_t* __restrict__ q,
                                                   const uint64_t* __restrict__ kc,
@@ -61,11 +378,10 @@ __global__ __launch_bounds__(NW * 64) void k_attn(const uint64_t* __restrict__ q
   constexpr int DH = DHW * 64;
   constexpr int NT = DH / 16;
   constexpr int NTH = NW * 64;
-  __shared__ int sNum[16][DH];
+  __shared__ AttnLut sLut;
+  __shared__ v4i sNum[NT * 64];  // [tile n][lane]: query c, channels 16n + 4g + e
   __shared__ int sDen[16];
-  __shared__ int sCnt[DH];
-  __shared__ uint64_t sKey[NW][64 * DHW];  // each wave's chunk of key rows
-  __shared__ uint64_t sVal[NW][DH];        // and its value words, one per channel
+  __shared__ AttnStage<DHW> sStage[kAttnStages * NW];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, c = lane & 15;
@@ -77,359 +393,279 @@ __global__ __launch_bounds__(NW * 64) void k_attn(const uint64_t* __restrict__ q
   const int qbps = gridDim.y / n_seq;               // query blocks per sequence
   const int sq = qbg / qbps, qb = qbg - sq * qbps;  // sequence, block within it
   const int Mt = n_seq * M, r0 = sq * M;            // rows per timestep, first row of sq
-  kc += sq * seq_words;
-  vt += sq * seq_words;
   const int d = H * DH, dw = d / 64;
-  const int capw = (int)(cap / 64);
   const int J = C + M;
   const int nch = (J + 63) / 64;
+  const uint64_t* kb = kc + sq * seq_words + (size_t)t * cap * dw + h * DHW;
+  const uint64_t* vb = vt + sq * seq_words + (size_t)t * (cap / 64) * d + h * DH;
 
-  const int lut_dw = lut_dword(lut, lane);
-  const int iq = qb * 16 + c;
-  uint64_t qw[DHW];
-#pragma unroll
-  for (int w = 0; w < DHW; ++w)
-    qw[w] = q[((size_t)t * Mt + r0 + min(iq, M - 1)) * dw + h * DHW + w];
-  for (int i = tid; i < 16 * DH; i += NTH) (&sNum[0][0])[i] = 0;
+  AttnChunk<DHW> first;
+  AttnWave<DHW, 1>::load(first, kb, vb, dw, d, min(wave, nch - 1), lane);
+  AttnWave<DHW, 1> w;
+  w.init(q + ((size_t)t * Mt + r0) * dw + h * DHW, dw, qb * 16, M - 1, g, c);
+  fill_lut(sLut, lut, tid, NTH);
+  for (int i = tid; i < NT * 64; i += NTH) sNum[i] = v4i{0, 0, 0, 0};
   if (tid < 16) sDen[tid] = 0;
-  for (int i = tid; i < DH; i += NTH) sCnt[i] = 0;
-
-  v4i acc[NT];
-  int cnt[NT];
-#pragma unroll
-  for (int i = 0; i < NT; ++i) {
-    acc[i] = v4i{0, 0, 0, 0};
-    cnt[i] = 0;
-  }
-  int den = 0;
-  // rows of queries past M (clamped loads) are scored too; they are never read
-
-  uint64_t* const sK = sKey[wave];
-  uint64_t* const sV = sVal[wave];
-  for (int jc = wave; jc < nch; jc += NW) {  // wave-uniform
-    const int j0 = jc * 64 + 16 * g;
-    // lane l loads key row jc*64 + l (rows past C+M read a valid row, masked
-    // when scored) and the chunk's rows meet in the wave's LDS buffer
-    const uint64_t* kr = kc + ((size_t)t * cap + min(jc * 64 + lane, J - 1)) * dw + h * DHW;
-    uint64_t kl[DHW];
-#pragma unroll
-    for (int w = 0; w < DHW; ++w) kl[w] = kr[w];
-    // lane l loads the chunk's value words of channels l, l + 64, ...
-    uint64_t vl[DHW];
-#pragma unroll
-    for (int w = 0; w < DHW; ++w) vl[w] = vt[((size_t)t * capw + jc) * d + h * DH + w * 64 + lane];
-    __builtin_amdgcn_sched_barrier(0);  // every load above is issued before the first use
-#pragma unroll
-    for (int w = 0; w < DHW; ++w) {
-      sK[lane * DHW + w] = kl[w];
-      sV[w * 64 + lane] = vl[w];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    uint32_t pk[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int s = 0; s < 16; ++s) {
-      int sc = 0;
-#pragma unroll
-      for (int w = 0; w < DHW; ++w) sc += __popcll(qw[w] & sK[(16 * g + s) * DHW + w]);
-      const bool jv = j0 + s < J;
-      const int pw = __builtin_amdgcn_ds_bpermute((sc >> 2) << 2, lut_dw);
-      const int p = jv ? (pw >> ((sc & 3) * 8)) & 0xFF : 0;
-      den += p;
-      pk[s >> 2] |= jv ? (uint32_t)((p - 128) & 0xFF) << ((s & 3) * 8) : 0u;
-    }
-    const v4i af = v4i{(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3]};
-    const int nvalid = J - j0;
-    const uint32_t vmask = nvalid >= 16 ? 0xFFFFu : (nvalid <= 0 ? 0u : ((1u << nvalid) - 1u));
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const uint32_t bits = (uint32_t)(sV[nt * 16 + c] >> (16 * g)) & vmask;
-      cnt[nt] += __popc(bits);
-      const v4i bf = v4i{(int)expand4_a(bits & 0xFu), (int)expand4_a((bits >> 4) & 0xFu),
-                         (int)expand4_a((bits >> 8) & 0xFu), (int)expand4_a(bits >> 12)};
-      acc[nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af, bf, acc[nt], 0, 0, 0);
-    }
-    __builtin_amdgcn_wave_barrier();  // the buffers' reads precede the next chunk's stores
-  }
-  __syncthreads();  // the partial sums are cleared
+  __syncthreads();
   if (wave < nch) {  // wave-uniform
+    w.run(kb, vb, dw, d, J, nch, wave, NW, sLut, &sStage[kAttnStages * wave], lane, g, c, first);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+    for (int n = 0; n < NT; ++n) {
+      const v4i x = w.acc[0][n];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) atomicAdd(&sNum[g * 4 + e][nt * 16 + c], acc[nt][e]);
-    atomicAdd(&sDen[c], den);
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) atomicAdd(&sCnt[nt * 16 + c], cnt[nt]);
+      for (int e = 0; e < 4; ++e) atomicAdd(reinterpret_cast<int*>(&sNum[n * 64 + lane]) + e, x[e]);
+    }
+    if (g == 0) atomicAdd(&sDen[c], w.den[0] + 128 * keys_of(wave, NW, nch, J));
   }
   __syncthreads();
 
   const bool small = J < 65536;
-  for (int i = tid; i < 16 * DH; i += NTH) {
-    const int qi = i / DH, ch = i - qi * DH;
-    const int iq2 = qb * 16 + qi;
-    if (iq2 < M) {
-      const long long num = (long long)sNum[qi][ch] + 128LL * sCnt[ch];
-      a_out[((size_t)t * Mt + r0 + iq2) * d + h * DH + ch] = attn_norm(num, sDen[qi], small);
+  for (int i = tid; i < NT * 64; i += NTH) {
+    const int n = i >> 6, lc = i & 15, lg = (i >> 4) & 3;
+    const int iq = qb * 16 + lc;
+    if (iq >= M) continue;
+    const v4i x = sNum[i];
+    const int den = sDen[lc];
+    v4i a;
+    if (small) {
+      a = attn_norm4(x, den);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] = attn_norm(x[e], den, false);
+    }
+    int32_t* o = a_out + ((size_t)t * Mt + r0 + iq) * d + h * DH + n * 16 + 4 * lg;
+    if ((reinterpret_cast<uintptr_t>(a_out) & 15) == 0) {  // uniform
+      *reinterpret_cast<v4i*>(o) = a;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = a[e];
     }
   }
 }
 
-// waves per workgroup: 16 for dh = 64; 8 or 12 for dh = 128 (its 16 keys of
-// two words per lane need more than the 128 registers of a 1024-thread group);
-// halved while the grid would not fit the chip in one round (many sequences:
-// fewer waves per workgroup take more key chunks each, the workgroups of all
-// sequences run at once)
-constexpr int kAttnWaves64 = 16, kAttnWaves128 = 8;
-// waves resident at once: 256 CUs x 16 (the kernels' registers allow 4-5
-// waves per SIMD)
-constexpr long long kAttnResidentWaves = 256LL * 16;
-constexpr long long kAttnCus = 256;
-
-struct AttnLaunch {
+// ---------------------------------------------------------------------------
+// k_attn_if: attention followed by the IF neuron of its output, in one kernel.
+// Workgroup = one head and 16*QG queries, wave = (timestep, part): the parts of
+// a timestep (PARTS, QG = 1: grids that leave SIMDs idle) take its chunks in
+// turn and add their sums in LDS; without parts a wave takes all chunks of its
+// timestep and normalises its sums itself.  The sums or currents meet in LDS
+// (16 queries at a time, over the chunks' stages) and the waves share the
+// tiles of 16 channels for the IF recurrence over t, the spike words and the
+// token's union over t.  a_out (the currents) and s_out are each optional.
+// No currents go through memory (64 MB written and read at the 2048-token
+// prompt below) and there is no launch between the two.
+// ---------------------------------------------------------------------------
+struct AttnIfArgs {
   const uint64_t* q;
   const uint64_t* kc;
   const uint64_t* vt;
   int64_t cap;
-  int T, M, C, H;
-  const uint8_t* lut;
-  int32_t* a_out;
-  int n_seq;
+  int T, M, C, H, n_seq, parts;
   int64_t seq_words;
+  const uint8_t* lut;
+  int32_t theta;
+  int32_t* a_out;
+  uint64_t* s_out;
+  uint64_t* u_out;
 };
 
-template <int DHW, int NW>
-static void attn_launch(const dim3& grid, const AttnLaunch& l, hipStream_t st) {
-  hipLaunchKernelGGL((k_attn<DHW, NW>), grid, dim3(NW * 64), 0, st, l.q, l.kc, l.vt, l.cap, l.T, l.M,
-                     l.C, l.H, l.lut, l.a_out, l.n_seq, l.seq_words);
-}
-
-nmdlm_status launch_attn(const uint64_t* q, const uint64_t* k_cache, const uint64_t* vt_cache,
-                         int64_t cap, int T, int M, int C, int H, int dh, const uint8_t* lut,
-                         int32_t* a_out, hipStream_t st, int n_seq, int64_t seq_words) {
-  if (n_seq < 1) return NMDLM_ERR_INVALID_ARG;
-  const dim3 grid(H, n_seq * ((M + 15) / 16), T);
-  const long long wgs = (long long)grid.x * grid.y * grid.z;
-  int nw = (dh == 64) ? kAttnWaves64 : kAttnWaves128;
-  // dh = 128: 12 waves (168 registers: three waves per SIMD, one workgroup
-  // per CU) when every workgroup has a CU of its own, so that 1024 + 32 keys
-  // take at most two chunks per wave instead of three (12-layer step 0.843
-  // -> 0.839 ms)
-  if (dh == 128 && wgs <= kAttnCus) nw = 12;
-  else while (nw > 4 && wgs * nw > kAttnResidentWaves) nw >>= 1;
-  const AttnLaunch l{q, k_cache, vt_cache, cap, T, M, C, H, lut, a_out, n_seq, seq_words};
-  switch (dh / 64 * 100 + nw) {
-    case 116: attn_launch<1, 16>(grid, l, st); break;
-    case 108: attn_launch<1, 8>(grid, l, st); break;
-    case 104: attn_launch<1, 4>(grid, l, st); break;
-    case 212: attn_launch<2, 12>(grid, l, st); break;
-    case 208: attn_launch<2, 8>(grid, l, st); break;
-    case 204: attn_launch<2, 4>(grid, l, st); break;
-    default:
-      return NMDLM_ERR_UNSUPPORTED;
-  }
-  return hip_status();
-}
-
-// ---------------------------------------------------------------------------
-// Attention followed by the IF neuron of its output, in one kernel.
-// Workgroup = one head and 16 block queries for every timestep.  Wave =
-// (timestep t, part): the parts of a timestep take 64-key chunks in turn and
-// add their partial sums into LDS.  Per chunk a lane loads one key (row =
-// lane) and the value bits of one channel (= lane), and the wave exchanges
-// them through LDS; chunks go in rounds of kRound whose loads are all issued
-// before the first is scored.  Then one wave per (query, 64-channel word)
-// computes a = floor(256 num / den) and runs the IF recurrence over t,
-// writing the spike words and the token's union over t.
-// ---------------------------------------------------------------------------
-constexpr int kRound = 4;
-
-template <int DHW>
-struct KvChunk {
-  uint64_t kw[DHW];  // key row jc*64 + lane, this head's words
-  uint64_t vw[DHW];  // value bits of channel w*64 + lane over the chunk's keys
-};
-
-template <int DHW>
-__device__ __forceinline__ void load_chunk(KvChunk<DHW>& ch, const uint64_t* __restrict__ kc,
-                                           const uint64_t* __restrict__ vt, int64_t cap, int capw,
-                                           int t, int h, int d, int dw, int J, int jc, int lane) {
-  constexpr int DH = DHW * 64;
-  const int jj = min(jc * 64 + lane, J - 1);  // past C+M: a valid row, masked when scored
-  const uint64_t* kr = kc + ((size_t)t * cap + jj) * dw + h * DHW;
-#pragma unroll
-  for (int w = 0; w < DHW; ++w) {
-    ch.kw[w] = kr[w];
-    ch.vw[w] = vt[((size_t)t * capw + jc) * d + h * DH + w * 64 + lane];
-  }
-}
-
-// sK, sV: this wave's 64 x DHW key words and DH value words in LDS
-// lut_dw: table bytes 4*lane .. 4*lane+3 (entry s is read from lane s/4)
-template <int DHW>
-__device__ __forceinline__ void score_chunk(const KvChunk<DHW>& ch, const uint64_t (&qw)[DHW],
-                                            int lut_dw, uint64_t* sK, uint64_t* sV, int J,
-                                            int jc, int lane, int g, int c, v4i (&acc)[DHW * 4],
-                                            int (&cnt)[DHW * 4], int& den) {
-  const int j0 = jc * 64 + 16 * g;
-#pragma unroll
-  for (int w = 0; w < DHW; ++w) {
-    sK[lane * DHW + w] = ch.kw[w];
-    sV[w * 64 + lane] = ch.vw[w];
-  }
-  __builtin_amdgcn_wave_barrier();
-  uint32_t pk[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-  for (int s = 0; s < 16; ++s) {
-    int sc = 0;
-#pragma unroll
-    for (int w = 0; w < DHW; ++w) sc += __popcll(qw[w] & sK[(16 * g + s) * DHW + w]);
-    const bool jv = j0 + s < J;
-    const int pw = __builtin_amdgcn_ds_bpermute((sc >> 2) << 2, lut_dw);
-    const int p = jv ? (pw >> ((sc & 3) * 8)) & 0xFF : 0;
-    den += p;
-    pk[s >> 2] |= jv ? (uint32_t)((p - 128) & 0xFF) << ((s & 3) * 8) : 0u;
-  }
-  const v4i af = v4i{(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3]};
-  const int nvalid = J - j0;
-  const uint32_t vmask = nvalid >= 16 ? 0xFFFFu : (nvalid <= 0 ? 0u : ((1u << nvalid) - 1u));
-#pragma unroll
-  for (int nt = 0; nt < DHW * 4; ++nt) {
-    const uint32_t bits = (uint32_t)(sV[nt * 16 + c] >> (16 * g)) & vmask;
-    cnt[nt] += __popc(bits);
-    const v4i bf = v4i{(int)expand4_a(bits & 0xFu), (int)expand4_a((bits >> 4) & 0xFu),
-                       (int)expand4_a((bits >> 8) & 0xFu), (int)expand4_a(bits >> 12)};
-    acc[nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af, bf, acc[nt], 0, 0, 0);
-  }
-  __builtin_amdgcn_wave_barrier();  // sK and sV are rewritten by the next chunk
-}
-
-template <int DHW, int NW>
-__global__ __launch_bounds__(NW * 64) void k_attn_if(const uint64_t* __restrict__ q,
-                                                     const uint64_t* __restrict__ kc,
-                                                     const uint64_t* __restrict__ vt, int64_t cap,
-                                                     int T, int M, int C, int H,
-                                                     const uint8_t* __restrict__ lut,
-                                                     int32_t theta, uint64_t* __restrict__ s_out,
-                                                     uint64_t* __restrict__ u_out) {
+template <int DHW, int QG, bool PARTS>
+__global__ __launch_bounds__(64 * NMDLM_MAX_T) void k_attn_if(AttnIfArgs a) {
   constexpr int DH = DHW * 64;
   constexpr int NT = DHW * 4;
-  constexpr int NTH = NW * 64;
-  __shared__ int sDen[NMDLM_MAX_T][16];
-  __shared__ int sCnt[NMDLM_MAX_T][DH];
-  __shared__ uint64_t sKey[NW][64 * DHW];
-  __shared__ uint64_t sVal[NW][DH];
-  extern __shared__ int sNum[];  // [T][16][DH]
+  static_assert(!PARTS || QG == 1, "parts: one query group");
+  __shared__ AttnLut sLut;
+  __shared__ int sDen[PARTS ? NMDLM_MAX_T : 1][16];
+  __shared__ uint32_t sWord[NMDLM_MAX_T][16][2 * DHW];  // halves of the spike words
+  // the waves' stages, then (chunks done) the sums [T][NT][64]
+  extern __shared__ v4i sNum[];
+  AttnStage<DHW>* sStage = reinterpret_cast<AttnStage<DHW>*>(sNum);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nth = blockDim.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nth >> 6;
   const int g = lane >> 4, c = lane & 15;
-  const int lid = xcd_order(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
-  const int h = lid % gridDim.x, qb = lid / gridDim.x;
-  const int d = H * DH, dw = d / 64;
-  const int capw = (int)(cap / 64);
-  const int J = C + M;
-  const int nch = (J + 63) / 64;
-  const int tp = T <= 1 ? 1 : (T <= 2 ? 2 : (T <= 4 ? 4 : 8));
-  const int NP = NW / tp;  // parts per timestep
-  const int t = wave / NP, part = wave - t * NP;
-  const bool active = t < T && part < nch;  // wave-uniform
-  const int tl = min(t, T - 1);             // idle waves load valid rows and discard them
+  const int nwg = gridDim.x * gridDim.y;
+  const int lid = xcd_order(blockIdx.x + gridDim.x * blockIdx.y, nwg);
+  const int h = lid % gridDim.x, qbg = lid / gridDim.x;
+  const int qbps = gridDim.y / a.n_seq;
+  const int sq = qbg / qbps, qb = qbg - sq * qbps;
+  const int Mt = a.n_seq * a.M, r0 = sq * a.M;
+  const int d = a.H * DH, dw = d / 64;
+  const int J = a.C + a.M, nch = (J + 63) / 64;
+  const int np = PARTS ? a.parts : 1;
+  const int t = PARTS ? wave / np : wave, part = wave - t * np;
+  const uint64_t* kb = a.kc + sq * a.seq_words + (size_t)t * a.cap * dw + h * DHW;
+  const uint64_t* vb = a.vt + sq * a.seq_words + (size_t)t * (a.cap / 64) * d + h * DH;
 
-  // table, query words and the first round of chunks: unconditional loads in
-  // one straight run, so each wait covers only what it needs
-  const int lut_dw = lut_dword(lut, lane);
-  const int iq = qb * 16 + c;
-  uint64_t qw[DHW];
-#pragma unroll
-  for (int w = 0; w < DHW; ++w) qw[w] = q[((size_t)tl * M + min(iq, M - 1)) * dw + h * DHW + w];
-  KvChunk<DHW> ch[kRound];
-#pragma unroll
-  for (int u = 0; u < kRound; ++u)
-    load_chunk<DHW>(ch[u], kc, vt, cap, capw, tl, h, d, dw, J, min(part + u * NP, nch - 1), lane);
-
-  for (int i = tid; i < NMDLM_MAX_T * 16; i += NTH) (&sDen[0][0])[i] = 0;
-  for (int i = tid; i < NMDLM_MAX_T * DH; i += NTH) (&sCnt[0][0])[i] = 0;
-  for (int i = tid; i < T * 16 * DH; i += NTH) sNum[i] = 0;
+  AttnChunk<DHW> first;
+  AttnWave<DHW, QG>::load(first, kb, vb, dw, d, min(part, nch - 1), lane);
+  AttnWave<DHW, QG> w;
+  w.init(a.q + ((size_t)t * Mt + r0) * dw + h * DHW, dw, qb * 16 * QG, a.M - 1, g, c);
+  fill_lut(sLut, a.lut, tid, nth);
   __syncthreads();
-
-  if (active) {
-#pragma unroll
-    for (int w = 0; w < DHW; ++w) qw[w] = iq < M ? qw[w] : 0ull;
-    v4i acc[NT];
-    int cnt[NT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      acc[i] = v4i{0, 0, 0, 0};
-      cnt[i] = 0;
-    }
-    int den = 0;
-    uint64_t* sK = sKey[wave];
-    uint64_t* sV = sVal[wave];
-    for (int jr = part;;) {
-#pragma unroll
-      for (int u = 0; u < kRound; ++u) {
-        const int jc = jr + u * NP;
-        if (jc < nch) score_chunk<DHW>(ch[u], qw, lut_dw, sK, sV, J, jc, lane, g, c, acc, cnt, den);
-      }
-      jr += kRound * NP;
-      if (jr >= nch) break;
-#pragma unroll
-      for (int u = 0; u < kRound; ++u)
-        load_chunk<DHW>(ch[u], kc, vt, cap, capw, t, h, d, dw, J, min(jr + u * NP, nch - 1), lane);
-    }
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (acc[nt][e]) atomicAdd(&sNum[(t * 16 + g * 4 + e) * DH + nt * 16 + c], acc[nt][e]);
-    if (den) atomicAdd(&sDen[t][c], den);
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-      if (cnt[nt]) atomicAdd(&sCnt[t][nt * 16 + c], cnt[nt]);
+  if (!PARTS || part < nch)  // wave-uniform
+    w.run(kb, vb, dw, d, J, nch, part, np, sLut, &sStage[kAttnStages * wave], lane, g, c, first);
+  __syncthreads();  // the stages are read
+  if constexpr (PARTS) {
+    for (int i = tid; i < a.T * NT * 64; i += nth) sNum[i] = v4i{0, 0, 0, 0};
+    for (int i = tid; i < a.T * 16; i += nth) (&sDen[0][0])[i] = 0;
+    __syncthreads();
   }
-  __syncthreads();
+  const bool small = J < 65536;
+  const bool vec = (reinterpret_cast<uintptr_t>(a.a_out) & 15) == 0;
 
-  for (int task = wave; task < 16 * DHW; task += NW) {
-    const int i = task / DHW, w = task - i * DHW;
-    const int iq2 = qb * 16 + i;
-    if (iq2 >= M) break;  // wave-uniform; later tasks have larger i
-    const int chn = w * 64 + lane;
-    long long V = 0;
-    uint64_t uor = 0ull;
-    for (int tt = 0; tt < T; ++tt) {
-      const long long num = (long long)sNum[(tt * 16 + i) * DH + chn] + 128LL * sCnt[tt][chn];
-      V += attn_norm(num, sDen[tt][i], J < 65536);
-      const bool s = V >= theta;
-      if (s) V -= theta;
-      const uint64_t word = __builtin_amdgcn_ballot_w64(s);
-      uor |= word;
-      if (lane == 0) s_out[((size_t)tt * M + iq2) * dw + h * DHW + w] = word;
+#pragma unroll
+  for (int u = 0; u < QG; ++u) {
+    if (u > 0) __syncthreads();  // the previous group's currents and words are read
+    const int iq0 = (qb * QG + u) * 16, iq = iq0 + c;
+    for (int i = tid; i < a.T * 32 * DHW; i += nth) (&sWord[0][0][0])[i] = 0u;
+    if constexpr (PARTS) {
+      if (part < nch) {
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            atomicAdd(reinterpret_cast<int*>(&sNum[(t * NT + n) * 64 + lane]) + e, w.acc[u][n][e]);
+        if (g == 0) atomicAdd(&sDen[t][c], w.den[u] + 128 * keys_of(part, np, nch, J));
+      }
+    } else {
+      const int den = w.den[u] + 128 * J;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        v4i x;
+        if (small) {
+          x = attn_norm4(w.acc[u][n], den);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[e] = attn_norm(w.acc[u][n][e], den, false);
+        }
+        sNum[(t * NT + n) * 64 + lane] = x;
+      }
     }
-    if (u_out && lane == 0) u_out[(size_t)iq2 * dw + h * DHW + w] = uor;
+    __syncthreads();
+    for (int n = wave; n < NT; n += nwaves) {
+      v4i V = v4i{0, 0, 0, 0};  // at most 256 T
+      for (int t0 = 0; t0 < a.T; t0 += 4) {
+        v4i cur[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int tt = min(t0 + k, a.T - 1);
+          cur[k] = sNum[(tt * NT + n) * 64 + lane];
+          if constexpr (PARTS) {
+            const int den = sDen[tt][c];
+            if (small) {
+              cur[k] = attn_norm4(cur[k], den);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) cur[k][e] = attn_norm(cur[k][e], den, false);
+            }
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int tt = t0 + k;
+          if (tt >= a.T) break;  // uniform
+          if (a.a_out && iq < a.M) {
+            int32_t* o = a.a_out + ((size_t)tt * Mt + r0 + iq) * d + h * DH + n * 16 + 4 * g;
+            if (vec) {
+              *reinterpret_cast<v4i*>(o) = cur[k];
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) o[e] = cur[k][e];
+            }
+          }
+          uint32_t bits = 0u;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            V[e] += cur[k][e];
+            const bool s = V[e] >= a.theta;
+            if (s) V[e] -= a.theta;
+            bits |= (uint32_t)s << e;
+          }
+          // tile n's 16 bits of the query's word, four from each lane group
+          atomicOr(&sWord[tt][c][n >> 1], bits << (16 * (n & 1) + 4 * g));
+        }
+      }
+    }
+    if (!a.s_out) continue;  // uniform
+    __syncthreads();
+    for (int i = tid; i < 16 * DHW * a.T; i += nth) {
+      const int k = i % DHW, m = (i / DHW) % 16, tt = i / (16 * DHW);
+      if (iq0 + m < a.M)
+        a.s_out[((size_t)tt * Mt + r0 + iq0 + m) * dw + h * DHW + k] =
+            sWord[tt][m][2 * k] | (uint64_t)sWord[tt][m][2 * k + 1] << 32;
+    }
+    if (a.u_out)
+      for (int i = tid; i < 16 * DHW; i += nth) {
+        const int k = i % DHW, m = i / DHW;
+        uint64_t uor = 0ull;
+        for (int tt = 0; tt < a.T; ++tt) uor |=
+            sWord[tt][m][2 * k] | (uint64_t)sWord[tt][m][2 * k + 1] << 32;
+        if (iq0 + m < a.M) a.u_out[(size_t)(r0 + iq0 + m) * dw + h * DHW + k] = uor;
+      }
   }
 }
 
-constexpr size_t kAttnIfMaxLds = 49152;  // bytes of [T][16][dh] partial sums
-
-nmdlm_status launch_attn_if(const uint64_t* q, const uint64_t* k_cache, const uint64_t* vt_cache,
-                            int64_t cap, int T, int M, int C, int H, int dh, const uint8_t* lut,
-                            int32_t theta, uint64_t* s_out, uint64_t* u_out, hipStream_t st) {
-  const size_t dyn = (size_t)T * 16 * dh * sizeof(int);
-  if (dyn > kAttnIfMaxLds || T > NMDLM_MAX_T) return NMDLM_ERR_UNSUPPORTED;
-  const dim3 grid(H, (M + 15) / 16);
-  switch (dh / 64) {
-    case 1:
-      hipLaunchKernelGGL((k_attn_if<1, 16>), grid, dim3(16 * 64), dyn, st, q, k_cache, vt_cache,
-                         cap, T, M, C, H, lut, theta, s_out, u_out);
-      break;
-    case 2:
-      hipLaunchKernelGGL((k_attn_if<2, 8>), grid, dim3(8 * 64), dyn, st, q, k_cache, vt_cache,
-                         cap, T, M, C, H, lut, theta, s_out, u_out);
-      break;
-    default:
-      return NMDLM_ERR_UNSUPPORTED;
-  }
+template <int DHW, int QG, bool PARTS = false>
+static nmdlm_status attn_if_launch(const AttnIfArgs& a, hipStream_t st) {
+  const dim3 grid(a.H, a.n_seq * ((a.M + 16 * QG - 1) / (16 * QG)));
+  const size_t dyn = std::max((size_t)a.T * DHW * 4 * 64 * sizeof(v4i),
+                              a.T * a.parts * kAttnStages * sizeof(AttnStage<DHW>));
+  if (dyn > 57344 &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_if<DHW, QG, PARTS>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn) != hipSuccess)
+    return NMDLM_ERR_HIP;
+  hipLaunchKernelGGL((k_attn_if<DHW, QG, PARTS>), grid, dim3(64 * a.T * a.parts), (uint32_t)dyn, st, a);
   return hip_status();
+}
+
+// Which kernel, all measured with spikes out, H = 16 unless said, dh = 64 / 128:
+//  * 32 queries a wave (QG = 2) halve the expansions and the staging per
+//    query but need two such waves per SIMD: T = 4, 2048 x 2048 keys 45.8 / 75.3
+//    us against 80.3 / 93.6 with 16; 600 x 1200 keys 20.2 / 29.0 against
+//    19.5 / 27.4.
+//  * Parts: where the waves of 16 queries leave SIMDs idle and a wave has
+//    chunks to share (T = 1, 1000 x 2000 keys, H = 8: 9.5 / 13.7 us against
+//    14.5 / 22.6; T = 4, 256 x 1256: 11.7 / 15.6 against 11.2 / 15.8; 9 chunks,
+//    T = 4: 8.8 against 7.5, so not below 12).
+//  * k_attn and the IF kernel, a second launch and the currents through
+//    memory, where few workgroups would each walk a long context: T = 4,
+//    32 x 1056 keys, dh = 128 11.5 us against 13.7 (8032 keys: 20 against 63);
+//    from 128 workgroups on (256 x 1256 keys) 17.2 / 31.0 against 11.2 / 15.8.
+constexpr int kAttnNW = 8;           // waves per workgroup of k_attn
+constexpr int kPartsMinChunks = 12;
+constexpr int kFusedMaxWalk = 6;     // chunks per wave of few workgroups with parts
+constexpr long long kFusedMinWgs = 128;
+constexpr long long kFullWaves = 2048;  // two waves per SIMD
+
+template <int DHW>
+static nmdlm_status launch_attention_dh(const AttnCall& c, hipStream_t st) {
+  const long long heads = (long long)c.H * c.n_seq;
+  const long long wgs = heads * ((c.M + 15) / 16);
+  const int nch = (c.C + c.M + 63) / 64;
+  AttnIfArgs a{c.q, c.k_cache, c.vt_cache, c.cap, c.T, c.M, c.C, c.H, c.n_seq, 1,
+               c.seq_words, c.lut, c.theta, c.a_out, c.s_out, c.u_out};
+  if (c.M >= 32 && heads * ((c.M + 31) / 32) * c.T >= kFullWaves) return attn_if_launch<DHW, 2>(a, st);
+  if (nch >= kPartsMinChunks && wgs * c.T < kFullWaves) a.parts = c.T <= 2 ? 4 : (c.T <= 4 ? 2 : 1);
+  if (c.fused || wgs >= kFusedMinWgs || nch < kPartsMinChunks ||
+      (nch + a.parts - 1) / a.parts <= kFusedMaxWalk)
+    return a.parts > 1 ? attn_if_launch<DHW, 1, true>(a, st) : attn_if_launch<DHW, 1>(a, st);
+  int32_t* const cur = c.a_out ? c.a_out : c.a_scratch;
+  hipLaunchKernelGGL((k_attn<DHW, kAttnNW>), dim3(c.H, c.n_seq * ((c.M + 15) / 16), c.T),
+                     dim3(kAttnNW * 64), 0, st, c.q, c.k_cache, c.vt_cache, c.cap, c.T, c.M, c.C, c.H,
+                     c.lut, cur, c.n_seq, c.seq_words);
+  const nmdlm_status rc = hip_status();
+  if (rc != NMDLM_OK || !c.s_out) return rc;
+  return launch_if(cur, c.T, c.n_seq * c.M, c.H * c.dh, c.theta, nullptr, nullptr, nullptr, c.s_out,
+                   st, c.u_out);
+}
+
+nmdlm_status launch_attention(const AttnCall& c, hipStream_t st) {
+  if (c.n_seq < 1) return NMDLM_ERR_INVALID_ARG;
+  if (c.dh == 64) return launch_attention_dh<1>(c, st);
+  if (c.dh == 128) return launch_attention_dh<2>(c, st);
+  return NMDLM_ERR_UNSUPPORTED;
 }
 
 }  // namespace nmdlm

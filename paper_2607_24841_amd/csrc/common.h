@@ -279,17 +279,28 @@ nmdlm_status launch_if(const int32_t* cur, int T, int M, int N, int32_t theta,
                        uint64_t* u_out = nullptr);
 nmdlm_status launch_qnl(const int32_t* x, int64_t n, int shift, int mode,
                         const uint8_t* lut, uint8_t* y, hipStream_t st);
-// n_seq sequences of M queries each (rows sequence-major); the caches of
-// sequence s start s * seq_words words after k_cache / vt_cache
-nmdlm_status launch_attn(const uint64_t* q, const uint64_t* k_cache,
-                         const uint64_t* vt_cache, int64_t cap, int T, int M, int C,
-                         int H, int dh, const uint8_t* lut, int32_t* a_out,
-                         hipStream_t st, int n_seq = 1, int64_t seq_words = 0);
-// attention with the IF of its output fused in (spikes and per-token union
-// over t); NMDLM_ERR_UNSUPPORTED when T*16*dh partial sums exceed its LDS
-nmdlm_status launch_attn_if(const uint64_t* q, const uint64_t* k_cache, const uint64_t* vt_cache,
-                            int64_t cap, int T, int M, int C, int H, int dh, const uint8_t* lut,
-                            int32_t theta, uint64_t* s_out, uint64_t* u_out, hipStream_t st);
+// One attention request: n_seq sequences of M queries each (rows
+// sequence-major); the caches of sequence s start s * seq_words words after
+// k_cache / vt_cache.  a_out (currents) and s_out (spikes of the IF over t,
+// with u_out the per-token union over t) are optional; a_scratch holds the
+// currents between two kernels when a_out is null.
+struct AttnCall {
+  const uint64_t* q;
+  const uint64_t* k_cache;
+  const uint64_t* vt_cache;
+  int64_t cap;
+  int T, M, C, H, dh;
+  int n_seq;
+  int64_t seq_words;
+  const uint8_t* lut;
+  int32_t theta;
+  int32_t* a_out;
+  int32_t* a_scratch;
+  uint64_t* s_out;
+  uint64_t* u_out;
+  bool fused;  // one kernel asked for (NMDLM_ATTN_FUSED)
+};
+nmdlm_status launch_attention(const AttnCall& c, hipStream_t st);
 nmdlm_status launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 nmdlm_status launch_ternary_encode(const int32_t* a, int M, int D, int K, int T, uint64_t* sp,
                                    uint64_t* sn, int64_t* s_sum, hipStream_t st);

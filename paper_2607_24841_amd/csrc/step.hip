@@ -437,17 +437,10 @@ nmdlm_status block_step_impl(const nmdlm_model* md, nmdlm_step_io* io, void* ws,
     attach_events(qkv, io, 4 * l + 0);
     if ((rc = launch_qbsm(qkv, b.qs, st)) != NMDLM_OK) return rc;
 
-    rc = NMDLM_ERR_UNSUPPORTED;
-    if ((io->flags & NMDLM_ATTN_FUSED) && n_seq == 1)
-      rc = launch_attn_if(b.Q, ly.k_cache, ly.vt_cache, cap, T, M, C, H, dh, ly.lut_att,
-                          ly.theta_a, b.A, b.uA, st);
-    if (rc == NMDLM_ERR_UNSUPPORTED) {
-      if ((rc = launch_attn(b.Q, ly.k_cache, ly.vt_cache, cap, T, Ms, C, H, dh, ly.lut_att, b.a,
-                            st, n_seq, seq_words)) != NMDLM_OK)
-        return rc;
-      rc = launch_if(b.a, T, M, d, ly.theta_a, nullptr, nullptr, nullptr, b.A, st, b.uA);
-    }
-    if (rc != NMDLM_OK) return rc;
+    AttnCall at{b.Q, ly.k_cache, ly.vt_cache, cap, T, Ms, C, H, dh, n_seq, seq_words, ly.lut_att,
+                ly.theta_a, nullptr, b.a, b.A, b.uA,
+                (io->flags & NMDLM_ATTN_FUSED) != 0 && n_seq == 1};
+    if ((rc = launch_attention(at, st)) != NMDLM_OK) return rc;
 
     QbsmCall o = base_call(b.A, T, M, d, ly.w_o, d, d, EPI_IF, io->flags, stl ? stl + 1 : nullptr);
     o.seg[0] = natural_seg(b.X1, sp_t, dw, ly.theta_o);

@@ -192,3 +192,36 @@ def test_attention_closed_forms_on_gpu():
     ones = np.ones_like(Vc)
     a1, _ = _attn_gpu(Q, Kc, ones, synth.sorted_lut_u8(synth.stream(1, 1)), cap, 50, 2, 64)
     assert (a1 == 256).all()
+
+
+# grids on either side of the choice between the attention kernels: one or two
+# query groups per wave, the key chunks of a wave shared by parts, and the
+# attention and IF kernels apart; ragged queries and keys in each
+ATTN_ROUTES = [  # T, M, C, H, dh
+    (4, 517, 0, 32, 64),        # two query groups, the last one empty of queries
+    (4, 1041, 3, 16, 128),      # two query groups, 17 of 32 queries in the last
+    (8, 500, 77, 16, 64),       # the same with eight timesteps
+    (1, 70, 1100, 2, 64),       # parts, four per timestep
+    (2, 33, 703, 4, 128),       # parts, twelve chunks, the last partial
+    (3, 130, 1007, 16, 64),     # parts, two per timestep
+    (5, 40, 640, 4, 128),       # eleven chunks, no parts
+    (4, 15, 750, 3, 128),       # twelve chunks over two parts
+    (4, 15, 760, 3, 128),       # thirteen chunks: the kernels apart
+    (8, 1000, 64600, 1, 64),    # 65600 keys in one kernel: the 64-bit quotient
+]
+
+
+@pytest.mark.parametrize("shape", ATTN_ROUTES,
+                         ids=[f"T{s[0]}M{s[1]}C{s[2]}H{s[3]}dh{s[4]}" for s in ATTN_ROUTES])
+def test_attention_kernel_choice_parity(shape):
+    T, M, C, H, dh = shape
+    Q, Kc, Vc, lut, cap = _attn_case(sum(shape), T, M, C, H, dh, 0.35)
+    lut[:] = np.sort(np.random.default_rng(M).integers(0, 256, 256))  # zero weights too
+    a_ref = O.bbm_attention(Q, Kc, Vc, C + M, H, lut)
+    a, s = _attn_gpu(Q, Kc, Vc, lut, cap, C, H, dh, theta=150)
+    assert_same(a, a_ref)
+    s_ref = O.if_neuron(a_ref, 150)[0]
+    assert_same(s, s_ref)
+    assert_same(_attn_spikes_gpu(Q, Kc, Vc, lut, cap, C, H, dh, 150), s_ref)
+    a0, s0 = _attn_gpu(Q, Kc, Vc, np.zeros(256, np.uint8), cap, C, H, dh, theta=1)
+    assert not a0.any() and not s0.any()              # no weight at all: the current is 0
