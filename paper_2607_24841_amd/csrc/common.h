@@ -226,6 +226,14 @@ struct QbsmCall {
   const int8_t* Wb;       // the weights in blocked operand order, or null
 };
 
+// The product over tiles of 128 block rows and 256 columns (tall.hip), row
+// blocks of 128 / T tokens, over blocked weights; tall_fits: the products it
+// takes (spikes without currents, bias or per-neuron thresholds, thresholds up
+// to 2^26; currents; head logits).
+bool tall_fits(const QbsmCall& c);
+nmdlm_status launch_tall(const QbsmArgs& a, int gx, int gy, hipStream_t st, hipEvent_t e0,
+                         hipEvent_t e1);
+
 // Blocked weight layout: for word w (rows 64w..64w+63) and column tile x
 // (columns 64x..64x+63), 4096 bytes at (w * ceil(N/64) + x) * 4096; within
 // them operand v (v = 0..3), lane l = 16g + c, byte j holds
