@@ -167,6 +167,7 @@ struct QbsmArgs {
   // 1.0f / ceil(K/64), 1.0f / Mb and 1.0f / seg_w (several segments): the
   // in-kernel quotients by div_small
   float inv_kw, inv_mb, inv_segw;
+  int n_tiles, n_rblk;       // lean product: output tiles, row blocks (a 1-D grid)
 };
 
 // Scratch used by one product (carved from a workspace).

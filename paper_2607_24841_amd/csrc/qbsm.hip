@@ -1160,6 +1160,150 @@ void k_qbsm_words(QbsmArgs a) {
   if (last) epilogue<NW>(a, sTile, ep[0], sUn, tid, lane, wave, x, y);
 }
 
+// ------------------------------------------------- lean product
+// The blocked product of few rows without the union: every word of the copy
+// is read, so a wave's weights can be asked for before any spike is known.
+// What bounds the products of a block step is the chain kernel arguments ->
+// spikes -> union -> weights -> reduction -> neurons, a memory round trip each
+// (k_qbsm_words, 128 x 2048 x 8192: 0.5, 1.6, 0.4, 4.4, 1.1 and 2.0 us, the
+// weights at HBM's rate while nothing else runs); here the spikes, residual words, table and the first DEPTH words of weights leave
+// in one straight run of loads (no branch between them: with one the compiler
+// waits for all of them at each use), and the weight stream runs while the
+// spikes are staged: 128 x 2048 x 6144, T = 4, cold weights 11.2 -> 8.6 us,
+// x 8192 11.8 -> 9.1, 128 x 2048 x 2048 7.3 -> 5.4, 64 x 1024 x 1024 6.2 -> 4.7,
+// 256 x 14336 x 4096 36.0 -> 24.8.
+// With statistics, the first workgroup counts them and does nothing else.
+template <int RT, int NW, int NL, int DEPTH>
+__global__ __launch_bounds__(NW * 64, RT == 4 && NW == 4 ? 4 : 1) __attribute__((aligned(1024)))
+void k_qbsm_lean(QbsmArgs a) {
+  constexpr int ROWS = RT * 16;
+  constexpr int NT = NW * 64;
+  __shared__ int sTile[ROWS * kTileLd];
+  __shared__ unsigned long long sUn[NW];
+  __shared__ EpiStage ep;
+  __shared__ int sStatCnt;
+  // the tile's spike rows as dwords, row stride 2*Kw+1; or the block union
+  extern __shared__ unsigned long long sDyn[];
+  uint32_t* sS = reinterpret_cast<uint32_t*>(sDyn);
+
+  touch_kernargs<sizeof(QbsmArgs)>();
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, c = lane & 15;
+  const int Kw = (a.K + 63) >> 6, gx = (a.N + 63) >> 6;
+  const int tiles = a.n_tiles;
+  const int extra = a.stats ? 1 : 0;
+  if (a.stats && blockIdx.x == 0) {  // uniform
+    stats_alone<NT>(a, sDyn, &sStatCnt, Kw, tid, lane);
+    return;
+  }
+  // row blocks of one column tile, then the next tile, on one XCD
+  const int lid = xcd_order((int)blockIdx.x - extra, tiles);
+  const int x = __builtin_amdgcn_readfirstlane(div_small(lid, a.inv_gy)), y = lid - x * a.n_rblk;
+  const int lds_row = 2 * Kw + 1, items = ROWS * Kw;
+
+  // item i: word i % Kw of tile row i / Kw, as an offset into S and into sS
+  // (bit 30: past the block, zeros; negative: past the tile)
+  auto spike_item = [&](int i, uint32_t& src, int& dst) {
+    const int ic = min(i, items - 1);
+    const int lr = div_small(ic, a.inv_kw), w = ic - lr * Kw;
+    const int t = div_small(lr, a.inv_mb), m = y * a.Mb + (lr - t * a.Mb);
+    src = (uint32_t)(min(t, a.T - 1) * a.M + min(m, a.M - 1)) * (uint32_t)Kw + w;
+    dst = i < items ? lr * lds_row + 2 * w : -1;
+    if (!(t < a.T && m < a.M)) dst |= 1 << 30;
+  };
+  auto store_spikes = [&](unsigned long long v, int dst) {
+    if (dst >= 0) {
+      if (dst >> 30) v = 0ull;
+      const int o = dst & ((1 << 30) - 1);
+      sS[o] = (uint32_t)v;
+      sS[o + 1] = (uint32_t)(v >> 32);
+    }
+  };
+  unsigned long long rv[NL];
+  int rdst[NL];
+  uint32_t src;
+  int i0 = tid;
+  for (; i0 - tid + NL * NT < items; i0 += NL * NT) {  // long K: whole batches first
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      spike_item(i0 + k * NT, src, rdst[k]);
+      rv[k] = a.S[src];
+    }
+#pragma unroll
+    for (int k = 0; k < NL; ++k) store_spikes(rv[k], rdst[k]);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  // ---- the last batch and every other load of the prologue
+#pragma unroll
+  for (int k = 0; k < NL; ++k) {
+    spike_item(i0 + k * NT, src, rdst[k]);
+    rv[k] = a.S[src];
+  }
+  const int rt = div_small(min(tid, a.T * a.Mb - 1), a.inv_mb);
+  const int rm = min(y * a.Mb + (min(tid, a.T * a.Mb - 1) - rt * a.Mb), a.M - 1);
+  const uint64_t* rsrc = a.resid ? a.resid + rt * a.rld_t + (int64_t)rm * a.rld_m + x : a.S;
+  const unsigned long long resid = *rsrc;
+  const uint8_t lut = *(a.lut ? a.lut + (tid & 255) : reinterpret_cast<const uint8_t*>(a.S));
+  const char* Wbb = reinterpret_cast<const char*>(a.Wb) + (size_t)x * 4096;  // uniform
+  const uint32_t lofs = (uint32_t)lane * 16u;
+  v4i b[DEPTH][4];
+  auto load_b = [&](int w, v4i (&q)[4]) {
+    const char* p = Wbb + (size_t)w * gx * 4096;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) q[v] = *reinterpret_cast<const v4i*>(p + (lofs + (uint32_t)(v * 1024)));
+  };
+#pragma unroll
+  for (int i = 0; i < DEPTH; ++i) load_b(min(wave + i * NW, Kw - 1), b[i]);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- staging
+  for (int i = tid; i < ROWS * kTileLd; i += NT) sTile[i] = 0;
+  for (int i = tid; i < NMDLM_MAX_T * 64; i += NT) ep.vbits[i] = 0u;
+  if (tid < 64) {
+    ep.bias[tid] = 0;
+    ep.theta[tid] = a.seg[a.nseg > 1 ? div_small(x * 64, a.inv_segw) : 0].theta;
+  }
+#pragma unroll
+  for (int k = 0; k < NL; ++k) store_spikes(rv[k], rdst[k]);
+  if (tid < a.T * a.Mb) ep.resid[tid] = resid;
+  if (tid < 256) ep.lut[tid] = (signed char)lut;
+  __syncthreads();
+
+  // ---- this wave's words: wave, wave + NW, ...
+  v4i acc[RT][4];
+#pragma unroll
+  for (int q = 0; q < RT; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[q][v] = v4i{0, 0, 0, 0};
+  const uint32_t* sA = sS + c * lds_row + (g >> 1);
+  const int sh = 16 * (g & 1);
+  auto mul = [&](int w, const v4i (&q)[4]) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      const v4i af = a_operand((sA[r * 16 * lds_row + 2 * w] >> sh) & 0xFFFFu);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        acc[r][v] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af, q[v], acc[r][v], 0, 0, 0);
+    }
+  };
+  // groups of DEPTH words; every group but the last asks for the next one's,
+  // word by word and without a condition, so that the waits stay exact
+  int w0 = wave;
+  for (; w0 + DEPTH * NW < Kw; w0 += DEPTH * NW) {  // wave-uniform
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) {
+      mul(w0 + i * NW, b[i]);
+      load_b(min(w0 + (i + DEPTH) * NW, Kw - 1), b[i]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < DEPTH; ++i)
+    if (w0 + i * NW < Kw) mul(w0 + i * NW, b[i]);  // wave-uniform
+  reduce_tile<RT>(acc, sTile, g, c);
+  __syncthreads();
+  epilogue<NW>(a, sTile, ep, sUn, tid, lane, wave, x, y);
+}
+
 // ------------------------------------------------- LDS-streamed product
 // Same tiles and operands as k_qbsm_words, but the active weight rows are
 // gathered straight into LDS (global_load_lds_dwordx4: 16 bytes per lane,
@@ -1600,6 +1744,8 @@ __global__ __launch_bounds__(NW * 64) void k_qbsm_list(QbsmArgs a) {
 // ---------------------------------------------------------------------------
 constexpr size_t kWordsLdsBudget = 81920;  // word product: two workgroups per CU fit in LDS
 constexpr int kWideMinTiles = 1536;  // output tiles (64 x 64) from which blocked products go wide
+constexpr long long kLeanMaxBytes = 1 << 24;  // weights read whole whatever the rows
+constexpr int kLeanTallWgs = 192;    // workgroups of 64-row lean tiles from which 32 rows give way
 constexpr int kCus = 256;            // compute units of the device
 // resident threads per compute unit of the word kernel: its variants take
 // 74-128 registers, four or five waves per SIMD, 16-20 waves per CU
@@ -1768,6 +1914,43 @@ nmdlm_status launch_weight_block(const int8_t* W, int K, int N, int64_t ldw, int
   return hip_status();
 }
 
+template <int RT, int NW, int NL, int DEPTH>
+static nmdlm_status launch_lean(const QbsmArgs& a, size_t dyn, hipStream_t st, hipEvent_t e0,
+                                hipEvent_t e1) {
+  if (dyn > 32768 &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_qbsm_lean<RT, NW, NL, DEPTH>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn) != hipSuccess)
+    return NMDLM_ERR_HIP;
+  hipExtLaunchKernelGGL((k_qbsm_lean<RT, NW, NL, DEPTH>), dim3(a.n_tiles + (a.stats ? 1 : 0)),
+                        dim3(NW * 64), (uint32_t)dyn, st, e0, e1, 0, a);
+  return hip_status();
+}
+
+// Waves of a lean workgroup: as k_qbsm_words for one and two row groups; four
+// row groups take eight where the grid or K is long for four (256 x 4096 x
+// 14336, 896 workgroups: 27.7 against 31.5 us; 128 x 2048 x 32000, 1000: 22.3
+// against 19.2).
+static int lean_waves(int RT, int Kw, int gx, const QbsmCall& c) {
+  if (RT != 4) return RT == 1 && Kw > 32 ? 16 : 8;
+  const int mb = 64 / c.T;
+  return Kw >= 64 || (long long)gx * ((c.M + mb - 1) / mb) <= kCus ? 8 : 4;
+}
+// LDS of k_qbsm_lean (mirrors its declarations) and its dynamic part
+static size_t lean_dyn(int RT, int Kw) {
+  return std::max((size_t)RT * 16 * (2 * Kw + 1) * 4, (size_t)Kw * 8);
+}
+static size_t lean_lds(int RT, int NW, int Kw) {
+  return (size_t)RT * 16 * kTileLd * 4 + (size_t)NW * 8 + sizeof(EpiStage) + 64 + lean_dyn(RT, Kw);
+}
+static nmdlm_status launch_lean_tile(const QbsmArgs& a, int RT, int NW, int Kw, hipStream_t st,
+                                     hipEvent_t e0, hipEvent_t e1) {
+  const size_t dyn = lean_dyn(RT, Kw);
+  if (RT == 1) return NW == 16 ? launch_lean<1, 16, 2, 4>(a, dyn, st, e0, e1)
+                               : launch_lean<1, 8, 2, 4>(a, dyn, st, e0, e1);
+  if (RT == 2) return launch_lean<2, 8, 4, 4>(a, dyn, st, e0, e1);
+  return NW == 8 ? launch_lean<4, 8, 8, 2>(a, dyn, st, e0, e1) : launch_lean<4, 4, 8, 2>(a, dyn, st, e0, e1);
+}
+
 // Static LDS of k_qbsm_words<RT, NW> and its dynamic part (mirror the declarations).
 // 64-row tiles of the one-tile kernel (not the scalar variant) keep the
 // reduction tile in the dynamic part, over the spike rows.
@@ -1854,6 +2037,23 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
       }
     }
   }
+  // lean product (every word of the copy, weights asked for before the
+  // spikes are known): unrequested, where the union of the block is dense or
+  // the matrix small enough that reading all of it costs less than waiting for
+  // the union.  Cold weights, k_qbsm_words against lean: 128 x 2048 x 6144 11.2 /
+  // 8.6 us, 128 x 8192 x 2048 14.6 / 11.8, 64 x 1024 x 4096 6.5 / 5.1; by rows,
+  // spike density 0.02: 32 x 2048 x 32000 12.8 / 13.3, 4 x 4096 x 14336 10.6 / 11.7,
+  // 4 x 4096 x 4096 10.7 / 8.5.
+  bool lean = path == 0 && !rt_forced && ((c.flags >> NMDLM_SPLIT_SHIFT) & 0xFFu) == 0 && c.Wb &&
+              !c.s_neg && !c.cur_out && !c.bias && !c.theta_vec &&
+              (c.mode == EPI_IF || c.mode == EPI_QNL_IF || c.mode == EPI_HEAD) &&
+              (R >= 64 || (long long)c.K * c.N <= kLeanMaxBytes);
+  // tall enough tiles read each weight from L2 fewer times: 64 rows, eight
+  // waves, while that leaves most CUs a workgroup (256 x 14336 x 4096 24.8
+  // against 32.3 us with 32 rows, 128 x 2048 x 6144 8.6 against 9.3)
+  if (lean && RT == 2 && 64 / c.T >= 1 &&
+      (long long)gx * ((c.M + 64 / c.T - 1) / (64 / c.T)) >= kLeanTallWgs)
+    RT = 4;
   while (RT > 1 && 16 * RT / 2 >= R && 16 * RT / 2 >= c.T) RT >>= 1;  // no empty tiles
   while (has_tr && RT > 1 && (16 * RT) / c.T > 32) RT >>= 1;  // channel-major: <= 32 tokens
   if (has_tr && c.seq_len > 0) {
@@ -1879,23 +2079,29 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
     const long long tiles4 = (long long)gx * ((c.M + mb4 - 1) / mb4);
     wide = path == 7 || tiles4 >= kWideMinTiles;
   }
+  lean = lean && lean_lds(RT, lean_waves(RT, Kw, gx, c), Kw) <= kDmaLdsMax;
   // tall tiles (128 rows x 256 columns a workgroup, see tall.hip), unrequested
   // only: where the grid has the workgroups to hide their chain of loads.  The
-  // line by the words of K, each measured either side, old against tall:
-  // K = 512: 32 workgroups 13.6 / 14.5 us, 64: 15.6 / 14.6; K = 1024: 64: 18.6 /
-  // 20.3, 112: 25.5 / 21.2; K = 2048 and 4096: 112: 31.4 / 33.6 and 45.1 / 56.5,
-  // 168: 44.0 / 33.7 and 63.4 / 56.5.
+  // line by the words of K, each measured either side (other / tall).  Against
+  // the lean product, cold weights: K = 512: 64 workgroups 8.7 / 10.4 us, 128:
+  // 11.0 / 10.5; K = 1024: 128: 13.1 / 14.3, 224: 20.8 / 15.7; K = 2048: 128: 16.6 /
+  // 23.8, 192: 28.0 / 22.9; K = 8192: 128: 53.6 / 72.1, 256: 134.8 / 73.8.  Against
+  // k_qbsm_words (currents): K = 512: 32: 13.6 / 14.5, 64: 15.6 / 14.6; K = 1024:
+  // 64: 18.6 / 20.3, 112: 25.5 / 21.2; K = 2048: 112: 31.4 / 33.6, 168: 44.0 / 33.7.
   bool tall = false;
   if (path == 0 && !rt_forced && ((c.flags >> NMDLM_SPLIT_SHIFT) & 0xFFu) <= 1u && tall_fits(c)) {
     const int mbt = 128 / c.T;
     const long long wgs = (long long)((gx + 3) / 4) * ((c.M + mbt - 1) / mbt);
-    tall = wgs >= (Kw <= 8 ? 48 : (Kw <= 16 ? 112 : 160));
+    // (fewer than two row blocks of 128 are mostly padding: 32 x 512 x 32000 8.4 / 11.3)
+    tall = (!lean || R >= 256) && wgs >= (lean ? (Kw <= 8 ? 112 : 160) : (Kw <= 8 ? 48 : (Kw <= 16 ? 112 : 160)));
   }
   if (tall) {
-    wide = false;
+    lean = wide = false;
     path = 3;
     RT = 8;
   }
+  if (wide) lean = false;
+  if (lean) path = 3;
   if (tern) {
     // ternary input: the word product only (both spike planes staged)
     path = 3;
@@ -1935,7 +2141,7 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
   } else if (path_auto && path == 3 && c.Wb && !tern) {
     blk = true;
   }
-  if (path == 3 && !wide && !tall && words_lds(RT, 4, Kw, tern, false, accum == 1) > kWordsLdsBudget) path = 1;
+  if (path == 3 && !wide && !tall && !lean && words_lds(RT, 4, Kw, tern, false, accum == 1) > kWordsLdsBudget) path = 1;
   if (path == 4 && dma_lds(RT, 4, 4, Kw) > kDmaLdsMax) path = 1;
   if (path > 4) path = 1;
   if (16 * RT < c.T) return NMDLM_ERR_UNSUPPORTED;
@@ -1953,7 +2159,7 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
   // 256 workgroups then share the weight rows instead of 64).  Elsewhere the
   // atomic accumulation costs more round trips than the split saves.
   int P = (int)((c.flags >> NMDLM_SPLIT_SHIFT) & 0xFFu);
-  if (P == 0 && path == 3 && !tern && !wide && !tall && tiles <= 64 && Kw >= 128) P = 4;
+  if (P == 0 && path == 3 && !tern && !wide && !tall && !lean && tiles <= 64 && Kw >= 128) P = 4;
   P = std::max(1, std::min(P, Kw));
   const size_t acc_elems = (size_t)16 * RT * 64 * (size_t)tiles;  // one accumulator tile per output tile
   if (P > 1 && (!scr.part || scr.part_elems < acc_elems)) P = 1;
@@ -2073,6 +2279,9 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
   a.Wb = blk || tall ? c.Wb : nullptr;
   a.blk_min = blk_min;
   if (tall) return launch_tall(a, gx, gy, st, c.ev_begin, c.ev_end);
+  a.n_tiles = tiles;
+  a.n_rblk = gy;
+  if (lean) return launch_lean_tile(a, RT, lean_waves(RT, Kw, gx, c), Kw, st, c.ev_begin, c.ev_end);
 
   const dim3 grid(gxl, gy, P);
   hipEvent_t e0 = c.ev_begin, e1 = c.ev_end;

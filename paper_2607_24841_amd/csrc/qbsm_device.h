@@ -172,4 +172,35 @@ __device__ __forceinline__ void stats_write(const QbsmArgs& a, int total) {
   a.stats->weight_bytes = (int64_t)total * (int64_t)a.N;
 }
 
+// The whole count by one workgroup that has nothing else to do: the union of
+// the sources' rows in sU [Kw], sixteen rows of a thread's word in flight.
+template <int NT>
+__device__ __forceinline__ void stats_alone(const QbsmArgs& a, unsigned long long* sU, int* sCnt, int Kw, int tid,
+                            int lane) {
+  if (tid == 0) *sCnt = 0;
+  for (int w = tid; w < Kw; w += NT) sU[w] = 0ull;
+  __syncthreads();
+  if (!a.dense) {
+    const uint64_t* src = a.upart ? a.upart : a.S;
+    const int nsrc = a.upart ? a.nparts : a.T * a.M;
+    const int per = min(Kw, NT), slices = NT / per, s0 = tid / per;
+    for (int w = tid - s0 * per; w < Kw && s0 < slices; w += per) {
+      unsigned long long u = 0ull;
+      for (int r = s0; r < nsrc; r += 16 * slices) {
+        unsigned long long v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = src[(size_t)min(r + k * slices, nsrc - 1) * Kw + w];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) u |= v[k];
+      }
+      if (u) atomicOr(&sU[w], u);
+    }
+    __syncthreads();
+  }
+  stats_count<NT>(a, sU, sCnt, Kw, tid, lane);
+  __syncthreads();
+  if (tid == 0) stats_write(a, *sCnt);
+}
+
+
 }  // namespace nmdlm

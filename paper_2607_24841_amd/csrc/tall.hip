@@ -293,7 +293,6 @@ __global__ __launch_bounds__(256, 2) __attribute__((aligned(1024))) void k_qbsm_
 #pragma unroll
   for (int p = 0; p < 8; ++p) expand_piece(s, 0, p);
   load_spikes(kTallWords, s);
-  if (tid == 0) sStatCnt = 0;
   __syncthreads();
 
   v4i acc[8][4];
@@ -336,14 +335,7 @@ __global__ __launch_bounds__(256, 2) __attribute__((aligned(1024))) void k_qbsm_
   if (a.stats && x == 0 && y == 0) {  // uniform
     // active rows of the whole block's union
     __syncthreads();
-    unsigned long long* sStat = reinterpret_cast<unsigned long long*>(sA);
-    for (int w = tid; w < Kw; w += 256) sStat[w] = 0ull;
-    __syncthreads();
-    stats_merge<256>(a, sStat, Kw, tid, stats_slice<256>(a, Kw, tid));
-    __syncthreads();
-    stats_count<256>(a, sStat, &sStatCnt, Kw, tid, lane);
-    __syncthreads();
-    if (tid == 0) stats_write(a, sStatCnt);
+    stats_alone<256>(a, reinterpret_cast<unsigned long long*>(sA), &sStatCnt, Kw, tid, lane);
   }
 }
 
