@@ -100,12 +100,26 @@ constexpr int kLutEntries = 132;  // scores 0..128, padded to a multiple of four
 struct AttnLut {
   int e[2][kLutEntries][2];
 };
-__device__ __forceinline__ void fill_lut(AttnLut& sLut, const uint8_t* __restrict__ lut, int tid,
-                                         int nth) {
-  for (int i = tid; i < kLutEntries; i += nth) {
-    const uint32_t v = (uint32_t)lut[i] ^ 0x80u;
+constexpr int kLutLoads = (kLutEntries + 63) / 64;  // for a workgroup of one wave
+struct LutRegs {
+  uint8_t v[kLutLoads];
+};
+// loads at clamped places, without a condition, to leave with the others
+__device__ __forceinline__ LutRegs load_lut(const uint8_t* __restrict__ lut, int tid, int nth) {
+  LutRegs r;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) sLut.e[b >> 1][i][b & 1] = (int)(v << (8 * b));
+  for (int k = 0; k < kLutLoads; ++k) r.v[k] = lut[min(tid + k * nth, kLutEntries - 1)];
+  return r;
+}
+__device__ __forceinline__ void fill_lut(AttnLut& sLut, const LutRegs& r, int tid, int nth) {
+#pragma unroll
+  for (int k = 0; k < kLutLoads; ++k) {
+    const int i = tid + k * nth;
+    if (i < kLutEntries) {
+      const uint32_t v = (uint32_t)r.v[k] ^ 0x80u;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) sLut.e[b >> 1][i][b & 1] = (int)(v << (8 * b));
+    }
   }
 }
 
@@ -148,18 +162,25 @@ struct AttnWave {
   int den[QG];  // sum of p - 128 of query c over this lane's keys
   int cnt[NT];  // ones of channel 16n + c over this lane's keys
 
-  // query rows r0 + 16u + c (clamped to the last valid row), channels of head h
-  __device__ __forceinline__ void init(const uint64_t* __restrict__ qrow, int dw, int iq0, int mlast,
-                                       int g, int c) {
+  // query rows iq0 + 16u + c (clamped to the last valid row), channels of head h
+  __device__ __forceinline__ static void load_queries(uint32_t (&raw)[QG],
+                                                      const uint64_t* __restrict__ qrow, int dw,
+                                                      int iq0, int mlast, int g, int c) {
 #pragma unroll
     for (int u = 0; u < QG; ++u) {
       const uint64_t* p = qrow + (size_t)min(iq0 + 16 * u + c, mlast) * dw;
+      if constexpr (DHW == 2) raw[u] = reinterpret_cast<const u32_alias*>(p)[g];
+      else raw[u] = reinterpret_cast<const u16_alias*>(p)[g];
+    }
+  }
+  __device__ __forceinline__ void init(const uint32_t (&raw)[QG]) {
+#pragma unroll
+    for (int u = 0; u < QG; ++u) {
+      const uint32_t w = raw[u];
       if constexpr (DHW == 2) {
-        const uint32_t w = reinterpret_cast<const u32_alias*>(p)[g];
         q[u][0] = query_bytes(w);
         q[u][1] = query_bytes(w >> 4);
       } else {
-        const uint32_t w = reinterpret_cast<const u16_alias*>(p)[g];
         q[u][0] = query_bytes(w | (w << 12));
       }
       den[u] = 0;
@@ -279,12 +300,11 @@ struct AttnWave {
   __device__ __forceinline__ void run(const uint64_t* __restrict__ kb, const uint64_t* __restrict__ vb,
                                       int dw, int d, int J, int nch, int jc0, int step,
                                       const AttnLut& sLut, AttnStage<DHW>* st, int lane,
-                                      int g, int c, const AttnChunk<DHW>& first) {
+                                      int g, int c, const AttnChunk<DHW>& first,
+                                      AttnChunk<DHW> nxt) {
     const char* lb = reinterpret_cast<const char*>(&sLut);
-    AttnChunk<DHW> nxt;
     int jc = jc0;
     AttnStage<DHW>*s0 = st, *s1 = st + 1, *s2 = st + 2;  // chunks j - 1, j, j + 1
-    load(nxt, kb, vb, dw, d, min(jc + step, nch - 1), lane);
     v4i s[QG][4], p[QG];
     uint32_t k[4], v[NT];
     put(first, *s0, lane);
@@ -399,16 +419,22 @@ __global__ __launch_bounds__(NW * 64) void k_attn(const uint64_t* __restrict__ q
   const uint64_t* kb = kc + sq * seq_words + (size_t)t * cap * dw + h * DHW;
   const uint64_t* vb = vt + sq * seq_words + (size_t)t * (cap / 64) * d + h * DH;
 
-  AttnChunk<DHW> first;
+  AttnChunk<DHW> first, next;
+  // every load of the prologue leaves before the first is waited for
+  const LutRegs lr = load_lut(lut, tid, NTH);
+  uint32_t qraw[1];
+  AttnWave<DHW, 1>::load_queries(qraw, q + ((size_t)t * Mt + r0) * dw + h * DHW, dw, qb * 16, M - 1, g, c);
   AttnWave<DHW, 1>::load(first, kb, vb, dw, d, min(wave, nch - 1), lane);
+  AttnWave<DHW, 1>::load(next, kb, vb, dw, d, min(wave + NW, nch - 1), lane);
+  __builtin_amdgcn_sched_barrier(0);
   AttnWave<DHW, 1> w;
-  w.init(q + ((size_t)t * Mt + r0) * dw + h * DHW, dw, qb * 16, M - 1, g, c);
-  fill_lut(sLut, lut, tid, NTH);
+  w.init(qraw);
+  fill_lut(sLut, lr, tid, NTH);
   for (int i = tid; i < NT * 64; i += NTH) sNum[i] = v4i{0, 0, 0, 0};
   if (tid < 16) sDen[tid] = 0;
   __syncthreads();
   if (wave < nch) {  // wave-uniform
-    w.run(kb, vb, dw, d, J, nch, wave, NW, sLut, &sStage[kAttnStages * wave], lane, g, c, first);
+    w.run(kb, vb, dw, d, J, nch, wave, NW, sLut, &sStage[kAttnStages * wave], lane, g, c, first, next);
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
       const v4i x = w.acc[0][n];
@@ -498,14 +524,21 @@ __global__ __launch_bounds__(64 * NMDLM_MAX_T) void k_attn_if(AttnIfArgs a) {
   const uint64_t* kb = a.kc + sq * a.seq_words + (size_t)t * a.cap * dw + h * DHW;
   const uint64_t* vb = a.vt + sq * a.seq_words + (size_t)t * (a.cap / 64) * d + h * DH;
 
-  AttnChunk<DHW> first;
+  AttnChunk<DHW> first, next;
+  // every load of the prologue leaves before the first is waited for
+  const LutRegs lr = load_lut(a.lut, tid, nth);
+  uint32_t qraw[QG];
+  AttnWave<DHW, QG>::load_queries(qraw, a.q + ((size_t)t * Mt + r0) * dw + h * DHW, dw, qb * 16 * QG,
+                                  a.M - 1, g, c);
   AttnWave<DHW, QG>::load(first, kb, vb, dw, d, min(part, nch - 1), lane);
+  AttnWave<DHW, QG>::load(next, kb, vb, dw, d, min(part + np, nch - 1), lane);
+  __builtin_amdgcn_sched_barrier(0);
   AttnWave<DHW, QG> w;
-  w.init(a.q + ((size_t)t * Mt + r0) * dw + h * DHW, dw, qb * 16 * QG, a.M - 1, g, c);
-  fill_lut(sLut, a.lut, tid, nth);
+  w.init(qraw);
+  fill_lut(sLut, lr, tid, nth);
   __syncthreads();
   if (!PARTS || part < nch)  // wave-uniform
-    w.run(kb, vb, dw, d, J, nch, part, np, sLut, &sStage[kAttnStages * wave], lane, g, c, first);
+    w.run(kb, vb, dw, d, J, nch, part, np, sLut, &sStage[kAttnStages * wave], lane, g, c, first, next);
   __syncthreads();  // the stages are read
   if constexpr (PARTS) {
     for (int i = tid; i < a.T * NT * 64; i += nth) sNum[i] = v4i{0, 0, 0, 0};
