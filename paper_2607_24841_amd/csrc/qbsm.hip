@@ -2011,6 +2011,23 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
         }
       }
     }
+    // one-group tiles of sixteen waves that oversubscribe the chip run in two
+    // rounds: the next height that is resident at once, while it keeps half the
+    // CUs busy (ternary 32 x 4096 x 14336, T = 8: 448 workgroups 20.8 us, 224: 15.1;
+    // 96 x 3000 x 5000: 17.8 / 12.1)
+    if (!found) {
+      const int mb1 = 16 / c.T;
+      const long long w1 = mb1 < 1 ? 0 : (long long)gx * ((c.M + mb1 - 1) / mb1);
+      if (w1 * words_waves(1, Kw) * 64 > (long long)kCus * kThreadsPerCu)
+        for (int r = 2; r <= std::min(rt_full, 4) && !found; r <<= 1) {
+          const int mb = (16 * r) / c.T;
+          const long long wgs = (long long)gx * ((c.M + mb - 1) / mb);
+          if (wgs >= kCus / 2 && wgs * words_waves(r, Kw) * 64 <= (long long)kCus * kThreadsPerCu) {
+            RT = r;
+            found = true;
+          }
+        }
+    }
     if (!found) {
       // no height keeps the grid resident: when even the tallest tiles
       // oversubscribe the chip, they re-read each weight tile the fewest times
@@ -2092,8 +2109,9 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
   if (path == 0 && !rt_forced && ((c.flags >> NMDLM_SPLIT_SHIFT) & 0xFFu) <= 1u && tall_fits(c)) {
     const int mbt = 128 / c.T;
     const long long wgs = (long long)((gx + 3) / 4) * ((c.M + mbt - 1) / mbt);
-    // (fewer than two row blocks of 128 are mostly padding: 32 x 512 x 32000 8.4 / 11.3)
-    tall = (!lean || R >= 256) && wgs >= (lean ? (Kw <= 8 ? 112 : 160) : (Kw <= 8 ? 48 : (Kw <= 16 ? 112 : 160)));
+    // (fewer than two row blocks of 128 are mostly padding: 32 x 512 x 32000 8.4 / 11.3,
+    // 48 x 1024 x 32000 15.1 / 20.9)
+    tall = R >= 256 && wgs >= (lean ? (Kw <= 8 ? 112 : 160) : (Kw <= 8 ? 48 : (Kw <= 16 ? 112 : 160)));
   }
   if (tall) {
     lean = wide = false;

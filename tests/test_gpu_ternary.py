@@ -211,3 +211,27 @@ def test_product_modified_if_full_size_ffn_up():
     s_ref, V_ref = O.modified_if(O.qbsm_ternary(s_in, c.W)[0], S_ref, D * c.K)
     assert_same(_planes_to_ternary(op, on, c.W.shape[1]), s_ref, "output spike planes")
     assert_same(v, V_ref, "final membrane x den")
+
+
+@pytest.mark.parametrize("T,M,K,N", [(8, 3, 2100, 8300), (8, 11, 2070, 4200), (4, 7, 2100, 8200)])
+def test_tiles_resident_at_once(T, M, K, N):
+    """Grids that oversubscribe the chip with one-group tiles of sixteen waves
+    take the next height that is resident: sums against the oracle."""
+    torch, B = need_gpu()
+    a = synth.ternary_activations(synth.stream(9, M), M, K)
+    W = synth.int8_uniform(synth.stream(9, 50), (K, N))
+    ldw = (N + 15) // 16 * 16
+    Wp = np.zeros((K, ldw), dtype=np.int8)
+    Wp[:, :N] = W
+    Kw = (K + 63) // 64
+    sp = torch.empty((T, M, Kw), dtype=torch.int64, device="cuda")
+    sn = torch.empty_like(sp)
+    acc = torch.full((M, N), 5, dtype=torch.int32, device="cuda")
+    B.nmdlm_ternary_encode(torch.from_numpy(a).cuda(), M, K, 2, T, sp, sn)
+    B.nmdlm_qbsm_ternary(sp, sn, T, M, K, torch.from_numpy(Wp).cuda(), N, ldw, acc,
+                         ws=B.workspace(B.nmdlm_qbsm_workspace_size(T, M, K, N)))
+    torch.cuda.synchronize()
+    q = sum((synth.unpack_bits(B.from_dev_bits(p), K).astype(np.int64) * s)
+            for p, s in ((sp, 1), (sn, -1)))
+    q = sum(q[t] << t for t in range(T))
+    assert_same(acc.cpu().numpy(), q @ W.astype(np.int64))
