@@ -96,7 +96,8 @@ TRAFFIC = {
     "mdlm12": {"sources_sha256": "fc86da0ff2f80f4b93457c5fe8375e7be50dccbc03ec8dba1b5897440c3dd954",
                "bytes_per_launch": 14211689.4},
 }
-PRODUCT_SOURCES = ("paper_2607_24841_amd/csrc/qbsm.hip", "paper_2607_24841_amd/csrc/common.h")
+PRODUCT_SOURCES = ("paper_2607_24841_amd/csrc/qbsm.hip", "paper_2607_24841_amd/csrc/qbsm_device.h",
+                   "paper_2607_24841_amd/csrc/tall.hip", "paper_2607_24841_amd/csrc/common.h")
 
 
 def product_sources_sha256():
@@ -560,7 +561,8 @@ def bench_mdlm12_step(args):
         "weight_skip_fraction": 1.0 - touched / dense,
         "touched_weight_bytes_per_step": touched,
         "touched_weight_GBps": touched / (ms_per_step * 1e-3) / 1e9,
-        "roofline": {"kernel": "k_qbsm_words (int8 MFMA spike product with fused epilogue; all "
+        "roofline": {"kernel": ("k_qbsm_lean" if args.weights == "blocked" else "k_qbsm_words") +
+                               " (int8 MFMA spike product with fused epilogue; all "
                                "49 product launches of the step)",
                      "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBPS, "traffic": traffic,

@@ -46,9 +46,11 @@ typedef enum nmdlm_status {
 #define NMDLM_FORCE_DENSE 0x1u   /* read every weight row: the un-skipped product */
 #define NMDLM_NO_HEAD     0x2u   /* block step without head/confidence/unmask    */
 #define NMDLM_ATTN_FUSED  0x4u   /* block step: attention and the IF of its output
-                                    in one kernel (one workgroup per head and 16
-                                    queries, all timesteps); default is two
-                                    kernels.  Results do not depend on it.      */
+                                    in one kernel (a workgroup per head and 16
+                                    queries, all timesteps); without it the
+                                    grid and the context decide between one
+                                    kernel and two.  Results do not depend on
+                                    it.                                         */
 /* bits 8..15 of the flags of nmdlm_qbsm: force the number of K splits
  * (0 = automatic).  Results do not depend on it. */
 #define NMDLM_SPLIT_SHIFT 8u
