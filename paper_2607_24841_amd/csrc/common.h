@@ -61,15 +61,18 @@ __device__ __forceinline__ void tile_coords(int& x, int& y, int& z) {
   x = (l / gy) % gx;
   z = l / (gy * gx);
 }
+// Grids of fewer workgroups than this take their tile coordinates as float
+// quotients (div_small, exact in that range).
+constexpr int kFloatGrid = 1 << 21;
 // With inv_gy = 1/gy and inv_gxy = 1/(gx gy) the quotients of grids of
-// fewer than 2^21 workgroups are taken in float (exact, see div_small), in
+// fewer than kFloatGrid workgroups are taken in float (exact, see div_small), in
 // place of the integer divisions the scalar unit emulates with some forty
 // instructions each.
 __device__ __forceinline__ void tile_coords_inv(int& x, int& y, int& z, float inv_gy,
                                                 float inv_gxy) {
   const int gx = gridDim.x, gy = gridDim.y;
   const int n = gx * gy * gridDim.z;
-  if (n >= (1 << 21)) {  // uniform
+  if (n >= kFloatGrid) {  // uniform
     tile_coords(x, y, z);
     return;
   }
@@ -276,6 +279,19 @@ struct QbsmLimits {
 
 QbsmLimits qbsm_limits_single(int T, int M, int K, int N);
 void carve_qbsm_scratch(Carver& cv, const QbsmLimits& L, QbsmScratch* s);
+
+// The kernel that a product takes and its tiling.
+enum QbsmKernel : int { KRN_LIST, KRN_FUSED, KRN_WORDS, KRN_WIDE, KRN_DMA, KRN_LEAN, KRN_TALL };
+struct QbsmPlan {
+  nmdlm_status status;  // anything but NMDLM_OK: the product is refused
+  QbsmKernel kernel;
+  int RT, Mb, gy;       // 16-row groups and tokens of a row block, row blocks
+  int P, NW;            // K splits, waves of a workgroup
+  int accum, blk_min;
+  bool blk;             // the blocked copy is given to the kernel
+  size_t dyn;           // dynamic LDS
+};
+QbsmPlan plan_qbsm(const QbsmCall& c, const QbsmScratch& scr);
 
 // Launchers (enqueue only; arguments already validated).
 // gy_out (optional): row blocks used, i.e. the number of partial unions

@@ -1,0 +1,53 @@
+// Host-side query of the choice of a product's kernel, for the tests (a test
+// of one kernel states that its sizes reach it).  Not part of the installed
+// header; launches nothing and needs no GPU.
+#include "common.h"
+
+using namespace nmdlm;
+
+extern "C" {
+
+struct nmdlm_plan_query {
+  int32_t mode;  // EpiMode
+  int32_t T, M, K, N;
+  int32_t blocked, bias, cur, theta_vec, ternary;  // presence of each
+  int32_t theta;
+  int32_t transposed;  // three segments of N / 3 columns, the last channel-major
+  int32_t pos0, seq_len;
+  uint32_t flags;
+};
+struct nmdlm_plan_answer {
+  int32_t status, kernel;  // nmdlm_status, QbsmKernel
+  int32_t rows, tokens, row_blocks, splits, waves;
+};
+
+void nmdlm_internal_plan(const nmdlm_plan_query* q, nmdlm_plan_answer* out) {
+  // pointers are only tested for presence
+  char* const some = reinterpret_cast<char*>(256);
+  QbsmCall c{};
+  c.T = q->T;
+  c.M = q->M;
+  c.K = q->K;
+  c.N = q->N;
+  c.ldw = q->N;
+  c.mode = q->mode;
+  c.Wb = q->blocked ? reinterpret_cast<int8_t*>(some) : nullptr;
+  c.bias = q->bias ? reinterpret_cast<int32_t*>(some) : nullptr;
+  c.cur_out = q->cur ? reinterpret_cast<int32_t*>(some) : nullptr;
+  c.theta_vec = q->theta_vec ? reinterpret_cast<int32_t*>(some) : nullptr;
+  c.s_neg = q->ternary ? reinterpret_cast<uint64_t*>(some) : nullptr;
+  c.nseg = q->transposed ? 3 : 1;
+  c.seg_w = q->transposed ? q->N / 3 : 1 << 30;
+  for (int i = 0; i < kMaxSeg; ++i) c.seg[i].theta = q->theta;
+  c.seg[2].transposed = q->transposed;
+  c.seg[2].pos0 = q->pos0;
+  c.seg[1].seq_len = c.seg[2].seq_len = c.seq_len = q->seq_len;
+  c.flags = q->flags;
+  Carver cv{some, 0, (size_t)-1, true};
+  QbsmScratch scr;
+  carve_qbsm_scratch(cv, qbsm_limits_single(q->T, q->M, q->K, q->N), &scr);
+  const QbsmPlan p = plan_qbsm(c, scr);
+  *out = nmdlm_plan_answer{p.status, p.kernel, 16 * p.RT, p.Mb, p.gy, p.P, p.NW};
+}
+
+}  // extern "C"

@@ -1942,9 +1942,8 @@ static size_t lean_dyn(int RT, int Kw) {
 static size_t lean_lds(int RT, int NW, int Kw) {
   return (size_t)RT * 16 * kTileLd * 4 + (size_t)NW * 8 + sizeof(EpiStage) + 64 + lean_dyn(RT, Kw);
 }
-static nmdlm_status launch_lean_tile(const QbsmArgs& a, int RT, int NW, int Kw, hipStream_t st,
+static nmdlm_status launch_lean_tile(const QbsmArgs& a, int RT, int NW, size_t dyn, hipStream_t st,
                                      hipEvent_t e0, hipEvent_t e1) {
-  const size_t dyn = lean_dyn(RT, Kw);
   if (RT == 1) return NW == 16 ? launch_lean<1, 16, 2, 4>(a, dyn, st, e0, e1)
                                : launch_lean<1, 8, 2, 4>(a, dyn, st, e0, e1);
   if (RT == 2) return launch_lean<2, 8, 4, 4>(a, dyn, st, e0, e1);
@@ -1976,7 +1975,14 @@ static size_t fused_static_lds(int RT, int NW) {
          (size_t)NW * 12 + bits * 8 + sizeof(EpiStage) + 64;
 }
 
-nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t st, int* gy_out) {
+// The kernel and tiling of a product, from its sizes, options and flags alone
+// (pointers are only tested for presence); nothing is launched.
+QbsmPlan plan_qbsm(const QbsmCall& c, const QbsmScratch& scr) {
+  QbsmPlan pl{};
+  const auto refuse = [&pl](nmdlm_status rc) {
+    pl.status = rc;
+    return pl;
+  };
   const int R = c.T * c.M;
   const int Kw = (c.K + 63) / 64;
   const int dense = (c.flags & NMDLM_FORCE_DENSE) ? 1 : 0;
@@ -2077,7 +2083,7 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
     // several sequences: a channel-major segment keeps every row block
     // within one sequence
     while (RT > 1 && c.seq_len % ((16 * RT) / c.T) != 0) RT >>= 1;
-    if (16 * RT < c.T || c.seq_len % ((16 * RT) / c.T) != 0) return NMDLM_ERR_UNSUPPORTED;
+    if (16 * RT < c.T || c.seq_len % ((16 * RT) / c.T) != 0) return refuse(NMDLM_ERR_UNSUPPORTED);
   }
   const bool tern = c.s_neg != nullptr;
   // wide tiles (a workgroup takes four 64-column tiles of a 64-row block,
@@ -2096,7 +2102,10 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
     const long long tiles4 = (long long)gx * ((c.M + mb4 - 1) / mb4);
     wide = path == 7 || tiles4 >= kWideMinTiles;
   }
-  lean = lean && lean_lds(RT, lean_waves(RT, Kw, gx, c), Kw) <= kDmaLdsMax;
+  // (its grid is one-dimensional, the tile coordinates a float quotient: from
+  // kFloatGrid tiles on the other kernels, which divide in integers there)
+  lean = lean && lean_lds(RT, lean_waves(RT, Kw, gx, c), Kw) <= kDmaLdsMax &&
+         (long long)gx * ((c.M + (16 * RT) / c.T - 1) / ((16 * RT) / c.T)) < kFloatGrid;
   // tall tiles (128 rows x 256 columns a workgroup, see tall.hip), unrequested
   // only: where the grid has the workgroups to hide their chain of loads.  The
   // line by the words of K, each measured either side (other / tall).  Against
@@ -2124,7 +2133,7 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
     // ternary input: the word product only (both spike planes staged)
     path = 3;
     while (RT > 1 && words_lds(RT, 4, Kw, true) > kWordsLdsBudget && !rt_forced) RT >>= 1;
-    if (words_lds(RT, 4, Kw, true) > kWordsLdsBudget || Kw > 256) return NMDLM_ERR_UNSUPPORTED;
+    if (words_lds(RT, 4, Kw, true) > kWordsLdsBudget || Kw > 256) return refuse(NMDLM_ERR_UNSUPPORTED);
   }
   if (path == 0 && !wide) {
     path = 3;
@@ -2150,27 +2159,26 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
     path = 6;
   }
   if (path == 6) {
-    if (!c.Wb || tern) return NMDLM_ERR_UNSUPPORTED;
+    if (!c.Wb || tern) return refuse(NMDLM_ERR_UNSUPPORTED);
     blk = true;
     blk_min = 0;
     path = 3;
     while (RT > 1 && words_lds(RT, 4, Kw) > kWordsLdsBudget && !rt_forced) RT >>= 1;
-    if (words_lds(RT, 4, Kw) > kWordsLdsBudget) return NMDLM_ERR_UNSUPPORTED;
+    if (words_lds(RT, 4, Kw) > kWordsLdsBudget) return refuse(NMDLM_ERR_UNSUPPORTED);
   } else if (path_auto && path == 3 && c.Wb && !tern) {
     blk = true;
   }
   if (path == 3 && !wide && !tall && !lean && words_lds(RT, 4, Kw, tern, false, accum == 1) > kWordsLdsBudget) path = 1;
   if (path == 4 && dma_lds(RT, 4, 4, Kw) > kDmaLdsMax) path = 1;
   if (path > 4) path = 1;
-  if (16 * RT < c.T) return NMDLM_ERR_UNSUPPORTED;
+  if (16 * RT < c.T) return refuse(NMDLM_ERR_UNSUPPORTED);
   const int Mb = (16 * RT) / c.T;
   // the tile heights lowered for LDS above keep a channel-major segment's
   // row blocks within one sequence, or the call is refused
-  if (has_tr && c.seq_len > 0 && !tall && c.seq_len % Mb != 0) return NMDLM_ERR_UNSUPPORTED;
+  if (has_tr && c.seq_len > 0 && !tall && c.seq_len % Mb != 0) return refuse(NMDLM_ERR_UNSUPPORTED);
   const int gy = (c.M + Mb - 1) / Mb;
   const int tiles = gx * gy;
-  if ((size_t)tiles > scr.n_counters) return NMDLM_ERR_WORKSPACE;
-  if (gy_out) *gy_out = gy;
+  if ((size_t)tiles > scr.n_counters) return refuse(NMDLM_ERR_WORKSPACE);
 
   // K splits: requested by the flags, or, unrequested, four ways for a short
   // grid over a long K (at most 64 output tiles, K of 128 words or more:
@@ -2212,8 +2220,35 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
     if (fused && !c.u_in && !dense && (long long)R * Kw > kUnionDirect) fused = false;
   }
 
-  const int gxl = wide || tall ? (gx + 3) / 4 : gx;  // grid columns
   if (wide) NW = 4;
+  pl.kernel = tall ? KRN_TALL : lean ? KRN_LEAN : wide ? KRN_WIDE : dma ? KRN_DMA
+              : words ? KRN_WORDS : fused ? KRN_FUSED : KRN_LIST;
+  pl.RT = RT;
+  pl.Mb = Mb;
+  pl.gy = gy;
+  pl.P = P;
+  pl.NW = lean ? lean_waves(RT, Kw, gx, c) : NW;
+  pl.accum = accum;
+  pl.blk = blk || tall;
+  pl.blk_min = blk_min;
+  pl.dyn = lean ? lean_dyn(RT, Kw) : dyn;
+  return pl;
+}
+
+nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t st, int* gy_out) {
+  const QbsmPlan pl = plan_qbsm(c, scr);
+  if (pl.status != NMDLM_OK) return pl.status;
+  const int R = c.T * c.M;
+  const int Kw = (c.K + 63) / 64;
+  const int dense = (c.flags & NMDLM_FORCE_DENSE) ? 1 : 0;
+  const int gx = (c.N + 63) / 64;
+  const int RT = pl.RT, Mb = pl.Mb, gy = pl.gy, P = pl.P, NW = pl.NW, tiles = gx * gy;
+  const size_t dyn = pl.dyn;
+  const bool tall = pl.kernel == KRN_TALL, lean = pl.kernel == KRN_LEAN, wide = pl.kernel == KRN_WIDE;
+  const bool dma = pl.kernel == KRN_DMA, words = pl.kernel == KRN_WORDS || wide;
+  const bool fused = pl.kernel == KRN_FUSED;
+  if (gy_out) *gy_out = gy;
+  const int gxl = wide || tall ? (gx + 3) / 4 : gx;  // grid columns
 
   nmdlm_status rc0 = NMDLM_OK;
   PrepArgs pa;
@@ -2233,7 +2268,7 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
   pa.counters = scr.counters;
   pa.n_counters = tiles;
   pa.sc = scr.sc;
-  if (!fused && !words && !dma) {
+  if (pl.kernel == KRN_LIST) {
     if (!dense && !pa.upart && (long long)R * Kw > kUnionDirect) {
       hipLaunchKernelGGL(k_union, dim3(Kw), dim3(256), 0, st, c.s_in, R, Kw, scr.U);
       pa.upart = scr.U;
@@ -2293,13 +2328,13 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
   a.thr_den = c.thr_den;
   a.s_neg_out = c.s_neg_out;
   a.v_out = c.v_out;
-  a.accum = accum;
-  a.Wb = blk || tall ? c.Wb : nullptr;
-  a.blk_min = blk_min;
+  a.accum = pl.accum;
+  a.Wb = pl.blk ? c.Wb : nullptr;
+  a.blk_min = pl.blk_min;
   if (tall) return launch_tall(a, gx, gy, st, c.ev_begin, c.ev_end);
   a.n_tiles = tiles;
   a.n_rblk = gy;
-  if (lean) return launch_lean_tile(a, RT, lean_waves(RT, Kw, gx, c), Kw, st, c.ev_begin, c.ev_end);
+  if (lean) return launch_lean_tile(a, RT, NW, dyn, st, c.ev_begin, c.ev_end);
 
   const dim3 grid(gxl, gy, P);
   hipEvent_t e0 = c.ev_begin, e1 = c.ev_end;
