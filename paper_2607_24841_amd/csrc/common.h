@@ -116,6 +116,24 @@ struct SpikeSeg {
   int64_t ld_s;
 };
 
+// Channel-major segments.  A row block's tokens are taken in runs of one
+// sequence each; a run is stored in plain bytes of the position words or by
+// clearing and setting its bits with atomics on whole words.  Several runs, of
+// several workgroups, meet in one word, so all of a segment's runs go the same
+// way: bytes where every run starts at a byte of its own.
+__host__ __device__ inline bool whole_bytes(const SpikeSeg& seg, int Mb) {
+  return ((seg.pos0 | Mb | seg.seq_len) & 7) == 0;
+}
+struct TokenRun {
+  int seq, pos, n;  // sequence, position of the first token, tokens
+};
+// The run of tokens m, m + 1, ... of which `left` remain in the row block.
+__host__ __device__ inline TokenRun token_run(const SpikeSeg& seg, int m, int left) {
+  if (seg.seq_len == 0) return TokenRun{0, seg.pos0 + m, left};
+  const int sq = m / seg.seq_len, off = m - sq * seg.seq_len, rest = seg.seq_len - off;
+  return TokenRun{sq, seg.pos0 + off, left < rest ? left : rest};
+}
+
 struct QbsmArgs {
   // operand prepared by the union/compaction kernels
   const uint64_t* sc;        // compacted spike bits [KSmax][R], R = T*M

@@ -1,6 +1,7 @@
-// Host-side query of the choice of a product's kernel, for the tests (a test
-// of one kernel states that its sizes reach it).  Not part of the installed
-// header; launches nothing and needs no GPU.
+// Host-side queries for the tests: the choice of a product's kernel (a test of
+// one kernel states that its sizes reach it) and the runs in which a row block
+// is stored channel-major.  Not part of the installed header; nothing is
+// launched and no GPU is needed.
 #include "common.h"
 
 using namespace nmdlm;
@@ -48,6 +49,23 @@ void nmdlm_internal_plan(const nmdlm_plan_query* q, nmdlm_plan_answer* out) {
   carve_qbsm_scratch(cv, qbsm_limits_single(q->T, q->M, q->K, q->N), &scr);
   const QbsmPlan p = plan_qbsm(c, scr);
   *out = nmdlm_plan_answer{p.status, p.kernel, 16 * p.RT, p.Mb, p.gy, p.P, p.NW};
+}
+
+// The runs of row block y of M tokens into out[4 i ..]: sequence, first position,
+// tokens, 1 when stored in bytes.  Returns their number.
+int nmdlm_internal_token_runs(int pos0, int seq_len, int Mb, int M, int y, int32_t* out) {
+  SpikeSeg seg{};
+  seg.pos0 = pos0;
+  seg.seq_len = seq_len;
+  const int yb = y * Mb, ntok = M - yb < Mb ? M - yb : Mb;
+  int n = 0;
+  for (int ml = 0; ml < ntok; ++n) {
+    const TokenRun r = token_run(seg, yb + ml, ntok - ml);
+    const int32_t v[4] = {r.seq, r.pos, r.n, whole_bytes(seg, Mb) ? 1 : 0};
+    for (int i = 0; i < 4; ++i) out[4 * n + i] = v[i];
+    ml += r.n;
+  }
+  return n;
 }
 
 }  // extern "C"

@@ -13,37 +13,30 @@ constexpr int kTallWords = 4;    // words (of 64 input channels) per LDS stage
 constexpr int kTallStage = kTallWords * (kTallRows / 16) * 64;  // 16-byte A operands per stage
 
 // Channel-major output of a tile's 64 columns (lane = column): token bits per
-// (step, column) in ep.vbits.  The row block's tokens are taken in runs of
-// one sequence each; whole bytes of the position words are stored plainly
-// (this workgroup owns them), other runs clear and set their bits with
-// atomics, as in the other product kernels.
+// (step, column) in ep.vbits, written run by run (see token_run).
 __device__ __forceinline__ void tall_channel_major(const QbsmArgs& a, const EpiStage& ep,
                                                    const SpikeSeg& seg, int segi, int lane, int n0,
                                                    int y) {
   if (n0 + lane >= a.N) return;
   const int ch = n0 + lane - segi * a.seg_w;
   const int yb = y * a.Mb, ntok = min(a.Mb, a.M - yb);
+  const bool bytes = whole_bytes(seg, a.Mb);
   for (int ml = 0; ml < ntok;) {  // uniform
-    const int m = yb + ml;
-    const int sq = seg.seq_len > 0 ? m / seg.seq_len : 0;
-    const int off = seg.seq_len > 0 ? m - sq * seg.seq_len : m;
-    const int run = seg.seq_len > 0 ? min(ntok - ml, seg.seq_len - off) : ntok;
-    const int p0 = seg.pos0 + off;
-    const uint32_t keep = run >= 32 ? 0xFFFFFFFFu : ((1u << run) - 1u);
-    uint64_t* base = seg.ptr + (int64_t)sq * seg.ld_s + (int64_t)ch * seg.ld_m;
-    const bool bytes = (p0 & 7) == 0 && (a.Mb & 7) == 0 && (seg.seq_len == 0 || (run & 7) == 0);
+    const TokenRun r = token_run(seg, yb + ml, ntok - ml);
+    const uint32_t keep = r.n >= 32 ? 0xFFFFFFFFu : ((1u << r.n) - 1u);
+    uint64_t* base = seg.ptr + (int64_t)r.seq * seg.ld_s + (int64_t)ch * seg.ld_m;
     for (int t = 0; t < a.T; ++t) {
       const uint32_t bits = (ep.vbits[t * 64 + lane] >> ml) & keep;
       uint64_t* row = base + t * seg.ld_t;
       if (bytes) {
-        for (int b = 0; b < (run + 7) >> 3; ++b) {
-          const int pb = (p0 >> 3) + b;
+        for (int b = 0; b < (r.n + 7) >> 3; ++b) {
+          const int pb = (r.pos >> 3) + b;
           reinterpret_cast<uint8_t*>(row + (int64_t)(pb >> 3) * seg.ld_p)[pb & 7] =
               (uint8_t)(bits >> (8 * b));
         }
       } else {
-        const int o = p0 & 63;
-        unsigned long long* w = reinterpret_cast<unsigned long long*>(row + (int64_t)(p0 >> 6) * seg.ld_p);
+        const int o = r.pos & 63;
+        unsigned long long* w = reinterpret_cast<unsigned long long*>(row + (int64_t)(r.pos >> 6) * seg.ld_p);
         const uint64_t m1 = o ? (uint64_t)keep >> (64 - o) : 0ull;
         atomicAnd(w, ~((uint64_t)keep << o));
         if (bits) atomicOr(w, (unsigned long long)((uint64_t)bits << o));
@@ -54,7 +47,7 @@ __device__ __forceinline__ void tall_channel_major(const QbsmArgs& a, const EpiS
         }
       }
     }
-    ml += run;
+    ml += r.n;
   }
 }
 

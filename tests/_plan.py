@@ -40,3 +40,11 @@ def step_plans(T, M, d, F, pos0=0, n_seq=1, V=0):
     if V:
         p["head"] = plan(T, R, d, V, mode=HEAD, blocked=1)
     return p
+
+
+def token_runs(pos0, seq_len, tokens, M, y):
+    """Runs of row block y (of `tokens` of the M tokens) in a channel-major
+    segment: (sequence, first position, tokens, stored in bytes)."""
+    out = (C.c_int32 * (4 * tokens))()
+    n = B.load().nmdlm_internal_token_runs(pos0, seq_len, tokens, M, y, out)
+    return [tuple(out[4 * i:4 * i + 4]) for i in range(n)]

@@ -6,7 +6,7 @@ import pytest
 torch = pytest.importorskip("torch")
 from paper_2607_24841_amd import binding as B  # noqa: E402
 
-from ._plan import plan  # noqa: E402
+from ._plan import plan, token_runs  # noqa: E402
 
 pytestmark = pytest.mark.skipif(not os.path.exists(B.LIB_PATH), reason="libnmdlm.so not built")
 
@@ -23,3 +23,28 @@ def test_lean_grids_stay_below_the_float_quotient(T, M, K, N):
     half = plan(T, M, K, N // 8, blocked=1)            # under the bound: lean again
     assert ((N // 8 + 63) // 64) * half.row_blocks < 1 << 21
     assert half.kernel == "lean"
+
+
+@pytest.mark.parametrize("tokens", [16, 32])
+@pytest.mark.parametrize("seq_len", [0, 4, 8, 10, 16, 20, 24, 33, 40, 72])
+@pytest.mark.parametrize("pos0", [0, 4, 8, 13, 60, 64])
+def test_channel_major_words_are_written_one_way(pos0, seq_len, tokens):
+    """The runs of all row blocks cover every token once; no position word is
+    written in bytes by one run and by atomics on the word by another, and no
+    byte is stored by two."""
+    M = 6 * seq_len if seq_len else 211
+    seen, ways, owner = set(), {}, {}
+    for y in range(-(-M // tokens)):
+        m = y * tokens
+        for i, (seq, pos, n, in_bytes) in enumerate(token_runs(pos0, seq_len, tokens, M, y)):
+            assert n > 0
+            for p in range(pos, pos + n):
+                assert (seq, p) == ((m // seq_len, pos0 + m % seq_len) if seq_len else (0, pos0 + m))
+                seen.add(m)
+                m += 1
+                ways.setdefault((seq, p // 64), set()).add(in_bytes)
+                if in_bytes:
+                    assert pos % 8 == 0
+                    assert owner.setdefault((seq, p // 8), (y, i)) == (y, i)
+    assert seen == set(range(M))
+    assert all(len(w) == 1 for w in ways.values())
