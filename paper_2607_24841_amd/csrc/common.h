@@ -144,7 +144,10 @@ struct QbsmArgs {
   int64_t ldw;
   int K, N;
   int T, M, Mb;              // Mb tokens per row block
-  int P;                     // K splits
+  union {
+    int P;                   // K splits
+    int n_rblk;              // lean product (no splits): row blocks, its grid being 1-D
+  };
   // epilogue
   int mode;
   const int32_t* bias;       // [N] or null
@@ -188,7 +191,6 @@ struct QbsmArgs {
   // 1.0f / ceil(K/64), 1.0f / Mb and 1.0f / seg_w (several segments): the
   // in-kernel quotients by div_small
   float inv_kw, inv_mb, inv_segw;
-  int n_tiles, n_rblk;       // lean product: output tiles, row blocks (a 1-D grid)
 };
 
 // Scratch used by one product (carved from a workspace).

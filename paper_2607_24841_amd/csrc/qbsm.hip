@@ -1190,14 +1190,13 @@ void k_qbsm_lean(QbsmArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, c = lane & 15;
   const int Kw = (a.K + 63) >> 6, gx = (a.N + 63) >> 6;
-  const int tiles = a.n_tiles;
   const int extra = a.stats ? 1 : 0;
   if (a.stats && blockIdx.x == 0) {  // uniform
     stats_alone<NT>(a, sDyn, &sStatCnt, Kw, tid, lane);
     return;
   }
   // row blocks of one column tile, then the next tile, on one XCD
-  const int lid = xcd_order((int)blockIdx.x - extra, tiles);
+  const int lid = xcd_order((int)blockIdx.x - extra, (int)gridDim.x - extra);
   const int x = __builtin_amdgcn_readfirstlane(div_small(lid, a.inv_gy)), y = lid - x * a.n_rblk;
   const int lds_row = 2 * Kw + 1, items = ROWS * Kw;
 
@@ -1915,13 +1914,13 @@ nmdlm_status launch_weight_block(const int8_t* W, int K, int N, int64_t ldw, int
 }
 
 template <int RT, int NW, int NL, int DEPTH>
-static nmdlm_status launch_lean(const QbsmArgs& a, size_t dyn, hipStream_t st, hipEvent_t e0,
+static nmdlm_status launch_lean(const QbsmArgs& a, int tiles, size_t dyn, hipStream_t st, hipEvent_t e0,
                                 hipEvent_t e1) {
   if (dyn > 32768 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(&k_qbsm_lean<RT, NW, NL, DEPTH>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn) != hipSuccess)
     return NMDLM_ERR_HIP;
-  hipExtLaunchKernelGGL((k_qbsm_lean<RT, NW, NL, DEPTH>), dim3(a.n_tiles + (a.stats ? 1 : 0)),
+  hipExtLaunchKernelGGL((k_qbsm_lean<RT, NW, NL, DEPTH>), dim3(tiles + (a.stats ? 1 : 0)),
                         dim3(NW * 64), (uint32_t)dyn, st, e0, e1, 0, a);
   return hip_status();
 }
@@ -1942,12 +1941,13 @@ static size_t lean_dyn(int RT, int Kw) {
 static size_t lean_lds(int RT, int NW, int Kw) {
   return (size_t)RT * 16 * kTileLd * 4 + (size_t)NW * 8 + sizeof(EpiStage) + 64 + lean_dyn(RT, Kw);
 }
-static nmdlm_status launch_lean_tile(const QbsmArgs& a, int RT, int NW, size_t dyn, hipStream_t st,
-                                     hipEvent_t e0, hipEvent_t e1) {
-  if (RT == 1) return NW == 16 ? launch_lean<1, 16, 2, 4>(a, dyn, st, e0, e1)
-                               : launch_lean<1, 8, 2, 4>(a, dyn, st, e0, e1);
-  if (RT == 2) return launch_lean<2, 8, 4, 4>(a, dyn, st, e0, e1);
-  return NW == 8 ? launch_lean<4, 8, 8, 2>(a, dyn, st, e0, e1) : launch_lean<4, 4, 8, 2>(a, dyn, st, e0, e1);
+static nmdlm_status launch_lean_tile(const QbsmArgs& a, int tiles, int RT, int NW, size_t dyn,
+                                     hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  if (RT == 1) return NW == 16 ? launch_lean<1, 16, 2, 4>(a, tiles, dyn, st, e0, e1)
+                               : launch_lean<1, 8, 2, 4>(a, tiles, dyn, st, e0, e1);
+  if (RT == 2) return launch_lean<2, 8, 4, 4>(a, tiles, dyn, st, e0, e1);
+  return NW == 8 ? launch_lean<4, 8, 8, 2>(a, tiles, dyn, st, e0, e1)
+                 : launch_lean<4, 4, 8, 2>(a, tiles, dyn, st, e0, e1);
 }
 
 // Static LDS of k_qbsm_words<RT, NW> and its dynamic part (mirror the declarations).
@@ -2332,9 +2332,10 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
   a.Wb = pl.blk ? c.Wb : nullptr;
   a.blk_min = pl.blk_min;
   if (tall) return launch_tall(a, gx, gy, st, c.ev_begin, c.ev_end);
-  a.n_tiles = tiles;
-  a.n_rblk = gy;
-  if (lean) return launch_lean_tile(a, RT, NW, dyn, st, c.ev_begin, c.ev_end);
+  if (lean) {
+    a.n_rblk = gy;
+    return launch_lean_tile(a, tiles, RT, NW, dyn, st, c.ev_begin, c.ev_end);
+  }
 
   const dim3 grid(gxl, gy, P);
   hipEvent_t e0 = c.ev_begin, e1 = c.ev_end;
