@@ -1745,6 +1745,8 @@ constexpr size_t kWordsLdsBudget = 81920;  // word product: two workgroups per C
 constexpr int kWideMinTiles = 1536;  // output tiles (64 x 64) from which blocked products go wide
 constexpr long long kLeanMaxBytes = 1 << 24;  // weights read whole whatever the rows
 constexpr int kLeanTallWgs = 192;    // workgroups of 64-row lean tiles from which 32 rows give way
+constexpr int kSplitTiles = 64;      // output tiles up to which, and
+constexpr int kSplitWords = 128;     // words of K from which a product is split over K
 constexpr int kCus = 256;            // compute units of the device
 // resident threads per compute unit of the word kernel: its variants take
 // 74-128 registers, four or five waves per SIMD, 16-20 waves per CU
@@ -2060,17 +2062,24 @@ QbsmPlan plan_qbsm(const QbsmCall& c, const QbsmScratch& scr) {
       }
     }
   }
-  // lean product (every word of the copy, weights asked for before the
-  // spikes are known): unrequested, where the union of the block is dense or
-  // the matrix small enough that reading all of it costs less than waiting for
-  // the union.  Cold weights, k_qbsm_words against lean: 128 x 2048 x 6144 11.2 /
-  // 8.6 us, 128 x 8192 x 2048 14.6 / 11.8, 64 x 1024 x 4096 6.5 / 5.1; by rows,
-  // spike density 0.02: 32 x 2048 x 32000 12.8 / 13.3, 4 x 4096 x 14336 10.6 / 11.7,
-  // 4 x 4096 x 4096 10.7 / 8.5.
+  // lean product (every word of the copy, weights asked for before the spikes
+  // are known): unrequested, for 64 rows or more, or a matrix of at most 16 MB.
+  // Not the union decides but the wait for it: at 64 rows and more reading all
+  // costs less at any share of active rows.  Cold weights, k_qbsm_words / lean:
+  // 64 x 4096 x 14336 at 1% active 16.1 / 14.6 us, 35% 19.1 / 14.5; 128 x 8192 x 8192 at 1%
+  // 21.4 / 17.5, 20% 27.9 / 17.6; 64 x 12000 x 2048 at 1% 17.0 / 16.7, 19% 19.6 / 16.4; 128 x
+  // 2048 x 6144 11.2 / 8.6, 64 x 1024 x 4096 6.5 / 5.1.  Below 64 rows: 32 x 2048 x 32000
+  // 12.8 / 13.3, 4 x 4096 x 14336 10.6 / 11.7, 4 x 4096 x 4096 10.7 / 8.5.  (A block without
+  // any spike is the exception: 25 x 6016 x 2048 7.0 / 12.3.)
+  // K beyond the word kernel's LDS: against the list kernels, which read the
+  // active rows alone, from 256 rows on (K = 34000, N = 512 at 82% active 94 / 34 us,
+  // at 19%, N = 1024, 33.4 / 35.7; 16 rows x 32768 x 512 at 2% 13.9 / 37.3, 128 rows at 11%
+  // 23.9 / 32.8).
+  const bool words_fit = words_lds(1, 4, Kw) <= kWordsLdsBudget;
   bool lean = path == 0 && !rt_forced && ((c.flags >> NMDLM_SPLIT_SHIFT) & 0xFFu) == 0 && c.Wb &&
               !c.s_neg && !c.cur_out && !c.bias && !c.theta_vec &&
               (c.mode == EPI_IF || c.mode == EPI_QNL_IF || c.mode == EPI_HEAD) &&
-              (R >= 64 || (long long)c.K * c.N <= kLeanMaxBytes);
+              (R >= 64 || (long long)c.K * c.N <= kLeanMaxBytes) && (words_fit || R >= 256);
   // tall enough tiles read each weight from L2 fewer times: 64 rows, eight
   // waves, while that leaves most CUs a workgroup (256 x 14336 x 4096 24.8
   // against 32.3 us with 32 rows, 128 x 2048 x 6144 8.6 against 9.3)
@@ -2102,10 +2111,21 @@ QbsmPlan plan_qbsm(const QbsmCall& c, const QbsmScratch& scr) {
     const long long tiles4 = (long long)gx * ((c.M + mb4 - 1) / mb4);
     wide = path == 7 || tiles4 >= kWideMinTiles;
   }
-  // (its grid is one-dimensional, the tile coordinates a float quotient: from
-  // kFloatGrid tiles on the other kernels, which divide in integers there)
-  lean = lean && lean_lds(RT, lean_waves(RT, Kw, gx, c), Kw) <= kDmaLdsMax &&
-         (long long)gx * ((c.M + (16 * RT) / c.T - 1) / ((16 * RT) / c.T)) < kFloatGrid;
+  if (lean) {
+    const int mbl = (16 * RT) / c.T;
+    const long long wgs = (long long)gx * ((c.M + mbl - 1) / mbl);
+    // its grid is one-dimensional, the tile coordinates a float quotient: from
+    // kFloatGrid tiles on the other kernels, which divide in integers there
+    lean = lean_lds(RT, lean_waves(RT, Kw, gx, c), Kw) <= kDmaLdsMax && wgs < kFloatGrid;
+    // a workgroup walks all of K, at 12.5 us for 8192 words' rows of cold weights:
+    // where k_qbsm_words splits a long K four ways, up to K = 10240, and to 16384
+    // for a matrix of at most 8 MB, which stays in the last-level cache between
+    // uses (split / lean: K = 8192, N = 2048 cold 14.0 / 12.6 us, cached 13.8 / 8.9; K = 12000,
+    // N = 1024 14.8 / 17.1, cached 14.8 / 11.6; K = 16384, N = 512 cached 15.4 / 13.6, N = 1024
+    // cold 16.3 / 21.4; K = 20000, N = 512 cold 17.1 / 25.3, cached 14.7 / 14.7)
+    if (words_fit && wgs <= kSplitTiles && Kw >= kSplitWords)
+      lean = lean && (Kw <= 160 || (Kw <= 256 && (long long)c.K * c.N <= kLeanMaxBytes / 2));
+  }
   // tall tiles (128 rows x 256 columns a workgroup, see tall.hip), unrequested
   // only: where the grid has the workgroups to hide their chain of loads.  The
   // line by the words of K, each measured either side (other / tall).  Against
@@ -2185,7 +2205,7 @@ QbsmPlan plan_qbsm(const QbsmCall& c, const QbsmScratch& scr) {
   // 256 workgroups then share the weight rows instead of 64).  Elsewhere the
   // atomic accumulation costs more round trips than the split saves.
   int P = (int)((c.flags >> NMDLM_SPLIT_SHIFT) & 0xFFu);
-  if (P == 0 && path == 3 && !tern && !wide && !tall && !lean && tiles <= 64 && Kw >= 128) P = 4;
+  if (P == 0 && path == 3 && !tern && !wide && !tall && !lean && tiles <= kSplitTiles && Kw >= kSplitWords) P = 4;
   P = std::max(1, std::min(P, Kw));
   const size_t acc_elems = (size_t)16 * RT * 64 * (size_t)tiles;  // one accumulator tile per output tile
   if (P > 1 && (!scr.part || scr.part_elems < acc_elems)) P = 1;

@@ -48,3 +48,26 @@ def test_channel_major_words_are_written_one_way(pos0, seq_len, tokens):
                     assert owner.setdefault((seq, p // 8), (y, i)) == (y, i)
     assert seen == set(range(M))
     assert all(len(w) == 1 for w in ways.values())
+
+
+@pytest.mark.parametrize("T,M,K,N,kernel,splits", [
+    (4, 4, 8192, 2048, "lean", 1),       # 32 tiles, 128 words: lean up to K = 10240
+    (4, 4, 12000, 1024, "words", 4),     # 16 tiles of cold weights: a long K is split four ways
+    (4, 4, 16384, 512, "lean", 1),       # 8 MB, in the last-level cache between uses
+    (4, 4, 16385, 512, "words", 4),
+    (4, 32, 20000, 512, "words", 4),     # 64 tiles
+    (4, 33, 20000, 512, "lean", 1),      # 72 tiles: no split, lean again
+    (4, 32, 34000, 512, "list", 1),      # beyond the word kernel's LDS: the active rows alone
+    (4, 63, 34000, 70, "list", 1),
+    (4, 64, 34000, 70, "lean", 1),       # 256 rows: most of the words are active
+    (4, 15, 4096, 14336, "words", 1),    # fewer than 64 rows of a large matrix
+    (4, 16, 4096, 14336, "lean", 1),
+])
+def test_lean_rule(T, M, K, N, kernel, splits):
+    """Where reading every word costs less than waiting for the union, and
+    where the row-load kernels are the faster ones."""
+    p = plan(T, M, K, N, blocked=1)
+    assert (p.status, p.kernel, p.splits) == (B.NMDLM_OK, kernel, splits)
+    for option in ("bias", "cur", "theta_vec"):            # never with these
+        assert plan(T, M, K, N, blocked=1, **{option: 1}).kernel != "lean"
+    assert plan(T, M, K, N).kernel != "lean"               # nor without the copy
