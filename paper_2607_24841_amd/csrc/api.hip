@@ -327,7 +327,7 @@ nmdlm_status nmdlm_bbm_attn(const uint64_t* q, const uint64_t* k_cache, const ui
     a = static_cast<int32_t*>(ws);
   }
   const AttnCall c{q, k_cache, vt_cache, cache_cap, T, M, C, H, dh, 1, 0, lut_att, theta_a, a_out,
-                   a, s_out, nullptr, false};
+                   a, s_out, nullptr, false, false};
   return launch_attention(c, static_cast<hipStream_t>(stream));
 }
 

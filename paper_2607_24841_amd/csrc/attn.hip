@@ -658,32 +658,65 @@ static nmdlm_status attn_if_launch(const AttnIfArgs& a, hipStream_t st) {
 //    query but need two such waves per SIMD: T = 4, 2048 x 2048 keys 45.8 / 75.3
 //    us against 80.3 / 93.6 with 16; 600 x 1200 keys 20.2 / 29.0 against
 //    19.5 / 27.4.
-//  * Parts: where the waves of 16 queries leave SIMDs idle and a wave has
-//    chunks to share (T = 1, 1000 x 2000 keys, H = 8: 9.5 / 13.7 us against
-//    14.5 / 22.6; T = 4, 256 x 1256: 11.7 / 15.6 against 11.2 / 15.8; 9 chunks,
-//    T = 4: 8.8 against 7.5, so not below 12).
+//  * Parts: where the waves of 16 queries leave SIMDs idle.  T = 1 (four; the
+//    parts also share the epilogue of what would be a workgroup of one wave):
+//    H = 8, 32 x 700 keys, dh = 128 7.4 us against 10.7; 1000 x 2000 9.5 / 13.7
+//    against 14.5 / 22.6; 4 x 480, dh = 64 4.8 against 6.3.  T = 2 (four) from 7 / 4
+//    chunks on: 7 chunks 6.0 / 7.8 against 6.1 / 8.8, 4 chunks of 64: 5.7 against
+//    5.4.  Below 12 chunks only while the parts run at once: T = 1, 300 workgroups, 10
+//    chunks, dh = 128 9.7 against 11.1, 672 workgroups, 6 chunks, dh = 64 7.9 against 7.4.
+//    T = 3, 4 (two) from 12: 256 x 1256 11.7 / 15.6 against 11.2 / 15.8; 9 chunks 8.8
+//    against 7.5.
 //  * k_attn and the IF kernel, a second launch and the currents through
-//    memory, where few workgroups would each walk a long context: T = 4,
-//    32 x 1056 keys, dh = 128 11.5 us against 13.7 (8032 keys: 20 against 63);
-//    from 128 workgroups on (256 x 1256 keys) 17.2 / 31.0 against 11.2 / 15.8.
+//    memory, where few workgroups would each walk a long context.  From 128
+//    workgroups on never (256 x 1256 keys 17.2 / 31.0 against 11.2 / 15.8); below,
+//    from 12 chunks on, when a wave walks more than 6: T = 4, 32 x 1056 keys,
+//    dh = 128 11.5 us against 13.7 (8032 keys: 20 against 63).  With few of them (up
+//    to one workgroup of k_attn per CU) also for shorter walks, by the chunk's
+//    cost (kWalk): inside a step, graph time, T = 4, dh = 128, 6 chunks 7.5 against
+//    8.3, 11 chunks 8.4 against 11.0; T = 8, dh = 64 5 chunks 7.5 against 7.7, 8 chunks
+//    7.5 against 8.8; T = 8, dh = 128 3 chunks 7.6 against 8.4, 8 chunks 8.5 against 11.7.
+//    A call by itself pays the host's pace for the second launch (11.3 us a call
+//    against 8.3): T = 4, dh = 128, 11 chunks 11.2 against 10.7; T = 8, 7 chunks 11.1 against
+//    11.4, 11 chunks 10.5 against 14.2.
 constexpr int kAttnNW = 8;           // waves per workgroup of k_attn
 constexpr int kPartsMinChunks = 12;
 constexpr int kFusedMaxWalk = 6;     // chunks per wave of few workgroups with parts
 constexpr long long kFusedMinWgs = 128;
 constexpr long long kFullWaves = 2048;  // two waves per SIMD
+// longest walk in one kernel with at most kOneRound workgroups of k_attn:
+// [step][dh / 64 - 1][T = 1, 2 | 3, 4 | 5, 6 | 7, 8] (T = 1, 2: as with parts)
+constexpr long long kOneRound = 256;
+constexpr int kWalk[2][2][4] = {{{11, 11, 11, 11}, {11, 11, 6, 6}}, {{11, 11, 5, 5}, {11, 5, 2, 1}}};
+
+AttnRoute attn_route(const AttnCall& c) {
+  const long long heads = (long long)c.H * c.n_seq;
+  const long long wgs = heads * ((c.M + 15) / 16);
+  const int nch = (c.C + c.M + 63) / 64, w = c.dh / 64 - 1;
+  AttnRoute r{1, 1, false};
+  if (c.M >= 32 && heads * ((c.M + 31) / 32) * c.T >= kFullWaves) {
+    r.groups = 2;
+    return r;
+  }
+  if (nch >= kPartsMinChunks) {
+    if (wgs * c.T < kFullWaves) r.parts = c.T <= 2 ? 4 : (c.T <= 4 ? 2 : 1);
+  } else if (wgs * c.T <= kFullWaves / 4 && (c.T == 1 || (c.T == 2 && nch >= (w ? 4 : 7)))) {
+    r.parts = 4;
+  }
+  if (c.fused || wgs >= kFusedMinWgs) return r;
+  const int walk = (nch + r.parts - 1) / r.parts;
+  r.split = (nch >= kPartsMinChunks && walk > kFusedMaxWalk) ||
+            (wgs * c.T <= kOneRound && walk > kWalk[c.step][w][(c.T - 1) / 2]);
+  return r;
+}
 
 template <int DHW>
 static nmdlm_status launch_attention_dh(const AttnCall& c, hipStream_t st) {
-  const long long heads = (long long)c.H * c.n_seq;
-  const long long wgs = heads * ((c.M + 15) / 16);
-  const int nch = (c.C + c.M + 63) / 64;
-  AttnIfArgs a{c.q, c.k_cache, c.vt_cache, c.cap, c.T, c.M, c.C, c.H, c.n_seq, 1,
-               c.seq_words, c.lut, c.theta, c.a_out, c.s_out, c.u_out};
-  if (c.M >= 32 && heads * ((c.M + 31) / 32) * c.T >= kFullWaves) return attn_if_launch<DHW, 2>(a, st);
-  if (nch >= kPartsMinChunks && wgs * c.T < kFullWaves) a.parts = c.T <= 2 ? 4 : (c.T <= 4 ? 2 : 1);
-  if (c.fused || wgs >= kFusedMinWgs || nch < kPartsMinChunks ||
-      (nch + a.parts - 1) / a.parts <= kFusedMaxWalk)
-    return a.parts > 1 ? attn_if_launch<DHW, 1, true>(a, st) : attn_if_launch<DHW, 1>(a, st);
+  const AttnRoute r = attn_route(c);
+  const AttnIfArgs a{c.q, c.k_cache, c.vt_cache, c.cap, c.T, c.M, c.C, c.H, c.n_seq, r.parts,
+                     c.seq_words, c.lut, c.theta, c.a_out, c.s_out, c.u_out};
+  if (r.groups == 2) return attn_if_launch<DHW, 2>(a, st);
+  if (!r.split) return r.parts > 1 ? attn_if_launch<DHW, 1, true>(a, st) : attn_if_launch<DHW, 1>(a, st);
   int32_t* const cur = c.a_out ? c.a_out : c.a_scratch;
   hipLaunchKernelGGL((k_attn<DHW, kAttnNW>), dim3(c.H, c.n_seq * ((c.M + 15) / 16), c.T),
                      dim3(kAttnNW * 64), 0, st, c.q, c.k_cache, c.vt_cache, c.cap, c.T, c.M, c.C, c.H,

@@ -344,7 +344,15 @@ struct AttnCall {
   uint64_t* s_out;
   uint64_t* u_out;
   bool fused;  // one kernel asked for (NMDLM_ATTN_FUSED)
+  bool step;   // one of a step's many kernels (not a call by itself)
 };
+// One kernel (k_attn_if) with `groups` x 16 queries a wave and `parts` waves per
+// timestep, or two (k_attn and the IF kernel).
+struct AttnRoute {
+  int groups, parts;
+  bool split;
+};
+AttnRoute attn_route(const AttnCall& c);
 nmdlm_status launch_attention(const AttnCall& c, hipStream_t st);
 nmdlm_status launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 nmdlm_status launch_ternary_encode(const int32_t* a, int M, int D, int K, int T, uint64_t* sp,

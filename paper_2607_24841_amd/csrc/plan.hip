@@ -51,6 +51,25 @@ void nmdlm_internal_plan(const nmdlm_plan_query* q, nmdlm_plan_answer* out) {
   *out = nmdlm_plan_answer{p.status, p.kernel, 16 * p.RT, p.Mb, p.gy, p.P, p.NW};
 }
 
+// The route of an attention call: 16-query groups of a wave, waves per timestep,
+// 1 when attention and IF are two kernels.
+void nmdlm_internal_attn_route(int T, int M, int C, int H, int dh, int n_seq, int fused, int step,
+                               int32_t* out) {
+  AttnCall c{};
+  c.T = T;
+  c.M = M;
+  c.C = C;
+  c.H = H;
+  c.dh = dh;
+  c.n_seq = n_seq;
+  c.fused = fused != 0;
+  c.step = step != 0;
+  const AttnRoute r = attn_route(c);
+  out[0] = r.groups;
+  out[1] = r.parts;
+  out[2] = r.split ? 1 : 0;
+}
+
 // The runs of row block y of M tokens into out[4 i ..]: sequence, first position,
 // tokens, 1 when stored in bytes.  Returns their number.
 int nmdlm_internal_token_runs(int pos0, int seq_len, int Mb, int M, int y, int32_t* out) {

@@ -439,7 +439,7 @@ nmdlm_status block_step_impl(const nmdlm_model* md, nmdlm_step_io* io, void* ws,
 
     AttnCall at{b.Q, ly.k_cache, ly.vt_cache, cap, T, Ms, C, H, dh, n_seq, seq_words, ly.lut_att,
                 ly.theta_a, nullptr, b.a, b.A, b.uA,
-                (io->flags & NMDLM_ATTN_FUSED) != 0 && n_seq == 1};
+                (io->flags & NMDLM_ATTN_FUSED) != 0 && n_seq == 1, true};
     if ((rc = launch_attention(at, st)) != NMDLM_OK) return rc;
 
     QbsmCall o = base_call(b.A, T, M, d, ly.w_o, d, d, EPI_IF, io->flags, stl ? stl + 1 : nullptr);

@@ -48,3 +48,10 @@ def token_runs(pos0, seq_len, tokens, M, y):
     out = (C.c_int32 * (4 * tokens))()
     n = B.load().nmdlm_internal_token_runs(pos0, seq_len, tokens, M, y, out)
     return [tuple(out[4 * i:4 * i + 4]) for i in range(n)]
+
+
+def attn_route(T, M, C_, H, dh, n_seq=1, fused=0, step=0):
+    """(16-query groups of a wave, waves per timestep, attention and IF in two kernels)."""
+    out = (C.c_int32 * 3)()
+    B.load().nmdlm_internal_attn_route(T, M, C_, H, dh, n_seq, fused, step, out)
+    return out[0], out[1], bool(out[2])

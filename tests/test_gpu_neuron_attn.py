@@ -7,6 +7,7 @@ from oracle import nmdlm_oracle as O
 from workloads import synth
 
 from ._gpu import assert_same, need_gpu
+from ._plan import attn_route
 
 pytestmark = pytest.mark.gpu
 
@@ -197,25 +198,35 @@ def test_attention_closed_forms_on_gpu():
 # grids on either side of the choice between the attention kernels: one or two
 # query groups per wave, the key chunks of a wave shared by parts, and the
 # attention and IF kernels apart; ragged queries and keys in each
-ATTN_ROUTES = [  # T, M, C, H, dh
-    (4, 517, 0, 32, 64),        # two query groups, the last one empty of queries
-    (4, 1041, 3, 16, 128),      # two query groups, 17 of 32 queries in the last
-    (8, 500, 77, 16, 64),       # the same with eight timesteps
-    (1, 70, 1100, 2, 64),       # parts, four per timestep
-    (2, 33, 703, 4, 128),       # parts, twelve chunks, the last partial
-    (3, 130, 1007, 16, 64),     # parts, two per timestep
-    (5, 40, 640, 4, 128),       # eleven chunks, no parts
-    (4, 15, 750, 3, 128),       # twelve chunks over two parts
-    (4, 15, 760, 3, 128),       # thirteen chunks: the kernels apart
-    (8, 1000, 64600, 1, 64),    # 65600 keys in one kernel: the 64-bit quotient
+ATTN_ROUTES = [  # T, M, C, H, dh; query groups, parts, kernels apart
+    (4, 517, 0, 32, 64, 2, 1, False),      # two query groups, the last one empty of queries
+    (4, 1041, 3, 16, 128, 2, 1, False),    # two query groups, 17 of 32 queries in the last
+    (8, 500, 77, 16, 64, 2, 1, False),     # the same with eight timesteps
+    (1, 70, 1100, 2, 64, 1, 4, False),     # parts, four per timestep
+    (1, 25, 7, 3, 128, 1, 4, False),       # one chunk: three parts without keys
+    (1, 600, 0, 16, 64, 1, 1, False),      # ten chunks, too many workgroups for parts
+    (2, 9, 300, 3, 128, 1, 4, False),      # five chunks over four parts
+    (2, 30, 330, 3, 64, 1, 1, False),      # six chunks of 64 channels: no parts
+    (2, 33, 703, 4, 128, 1, 4, False),     # parts, twelve chunks, the last partial
+    (3, 130, 1007, 16, 64, 1, 2, False),   # parts, two per timestep
+    (5, 40, 340, 4, 128, 1, 1, False),     # six chunks, no parts
+    (5, 40, 640, 4, 128, 1, 1, True),      # eleven chunks: the kernels apart
+    (7, 3, 420, 2, 128, 1, 1, True),
+    (4, 15, 750, 3, 128, 1, 2, False),     # twelve chunks over two parts
+    (4, 15, 760, 3, 128, 1, 2, True),      # thirteen chunks: the kernels apart
+    (8, 1000, 64600, 1, 64, 1, 1, True),   # 65600 keys: the 64-bit quotient
+    (1, 128, 65500, 16, 64, 1, 4, False),  # and in one kernel, with parts
+    (5, 128, 65500, 16, 64, 1, 1, False),  # and without
 ]
 
 
 @pytest.mark.parametrize("shape", ATTN_ROUTES,
                          ids=[f"T{s[0]}M{s[1]}C{s[2]}H{s[3]}dh{s[4]}" for s in ATTN_ROUTES])
 def test_attention_kernel_choice_parity(shape):
-    T, M, C, H, dh = shape
-    Q, Kc, Vc, lut, cap = _attn_case(sum(shape), T, M, C, H, dh, 0.35)
+    need_gpu()
+    T, M, C, H, dh = shape[:5]
+    assert attn_route(T, M, C, H, dh) == shape[5:]
+    Q, Kc, Vc, lut, cap = _attn_case(T + M + C + H + dh, T, M, C, H, dh, 0.35)
     lut[:] = np.sort(np.random.default_rng(M).integers(0, 256, 256))  # zero weights too
     a_ref = O.bbm_attention(Q, Kc, Vc, C + M, H, lut)
     a, s = _attn_gpu(Q, Kc, Vc, lut, cap, C, H, dh, theta=150)

@@ -6,7 +6,7 @@ import pytest
 torch = pytest.importorskip("torch")
 from paper_2607_24841_amd import binding as B  # noqa: E402
 
-from ._plan import plan, token_runs  # noqa: E402
+from ._plan import attn_route, plan, token_runs  # noqa: E402
 
 pytestmark = pytest.mark.skipif(not os.path.exists(B.LIB_PATH), reason="libnmdlm.so not built")
 
@@ -71,3 +71,23 @@ def test_lean_rule(T, M, K, N, kernel, splits):
     for option in ("bias", "cur", "theta_vec"):            # never with these
         assert plan(T, M, K, N, blocked=1, **{option: 1}).kernel != "lean"
     assert plan(T, M, K, N).kernel != "lean"               # nor without the copy
+
+
+def test_attention_route():
+    """One kernel or two, and the parts of a timestep."""
+    # one timestep: four parts of any context, while they run at once
+    assert attn_route(1, 25, 7, 16, 128) == (1, 4, False)
+    assert attn_route(1, 32, 700, 8, 128, step=1) == (1, 4, False)
+    assert attn_route(1, 600, 0, 16, 64) == (1, 1, False)
+    assert attn_route(2, 31, 480, 8, 128) == (1, 4, False)
+    # many timesteps: a long walk of few workgroups is shared by eight waves
+    assert attn_route(8, 31, 640, 8, 128) == (1, 1, True)
+    assert attn_route(8, 100, 560, 16, 128) == (1, 1, False)     # 896 workgroups of k_attn
+    # a step does not pay the host's pace for the second launch
+    for T, M, C, H, dh in ((4, 7, 350, 8, 128), (5, 7, 150, 4, 128), (8, 7, 100, 4, 128), (8, 7, 350, 8, 64)):
+        assert attn_route(T, M, C, H, dh) == (1, 1, False)
+        assert attn_route(T, M, C, H, dh, step=1) == (1, 1, True)
+        assert attn_route(T, M, C, H, dh, step=1, fused=1) == (1, 1, False)
+    assert attn_route(4, 16, 512, 16, 64, step=1) == (1, 1, False)
+    assert attn_route(4, 32, 1024, 16, 128, step=1) == (1, 2, True)
+    assert attn_route(8, 16, 300, 16, 64, n_seq=4, step=1) == (1, 1, False)   # 512 workgroups of k_attn
