@@ -8,37 +8,27 @@
 // Both products run on v_mfma_i32_16x16x64_i8, exact in int32: the scores as
 // a 0/1-byte product of key and query bits over the head's channels, the
 // weighted sum with p - 128 (signed byte) against the value bits expanded to
-// bytes, to which 128 * (number of ones of V[.,c]) is added back.
+// bytes, to which 128 * (number of ones of V[.,c]) is added back.  A sum is at
+// most 255 per key: below 2^31 up to NMDLM_MAX_KEYS keys.
 #include <algorithm>
 
 #include "common.h"
 
 namespace nmdlm {
 
-// floor(256 * num / den) for 0 <= num <= den (0 when den = 0).  For fewer
-// than 65536 keys, a = 256 num < 2^32 and den < 2^24: the quotient (at most
-// 256) is estimated as a float product with the hardware reciprocal, whose
-// relative error (a few units of 2^-24) keeps the estimate within one of
-// the exact floor, and one remainder test corrects it (the remainder
-// a - q den lies in (-2 den, 2 den), exact in wrapped 32-bit arithmetic).
-// Larger key counts divide in 64 bits.
-__device__ __forceinline__ int32_t attn_norm(long long num, long long den, bool small) {
-  if (den <= 0) return 0;
-  if (small) {
-    const uint32_t a = 256u * (uint32_t)num, b = (uint32_t)den;
-    uint32_t q = (uint32_t)((float)a * __builtin_amdgcn_rcpf((float)b));
-    const int32_t r = (int32_t)(a - __umul24(q, b));
-    if (r < 0) --q;
-    else if ((uint32_t)r >= b) ++q;
-    return (int32_t)q;
-  }
-  return (int32_t)((256LL * num) / den);
+static_assert(255LL * NMDLM_MAX_KEYS < 1LL << 31, "sums of table weights fit int32");
+
+// floor(256 * num / den) for 0 <= num <= den (0 when den = 0): from 65536 keys
+// on, in 64 bits.  (num and den themselves stay below 2^31 up to
+// NMDLM_MAX_KEYS keys of weight 255.)
+__device__ __forceinline__ int32_t attn_norm(int num, int den) {
+  return den <= 0 ? 0 : (int32_t)((256LL * num) / den);
 }
 
-// The same for four numerators over one denominator, fewer than 65536 keys
-// (0 <= num <= den < 2^24): k = 256 / den, lowered by 2^-20 of itself, more
-// than the rounding errors of the reciprocal and the two products (4 units of
-// 2^-24), so the truncated estimate is the floor or one below it; the
+// The same for four numerators over one denominator and fewer than 65536 keys
+// (num and den below 2^24, exact as floats): k = 256 / den, lowered by 2^-20 of
+// itself, more than the rounding errors of the reciprocal and the two products
+// (4 units of 2^-24), so the truncated estimate is the floor or one below it; the
 // remainder 256 num - q den, one rounding of an exact value, decides which.
 // An empty denominator (num = 0) counts as one.
 __device__ __forceinline__ v4i attn_norm4(v4i num, int den_i) {
@@ -457,7 +447,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn(const uint64_t* __restrict__ q
       a = attn_norm4(x, den);
     } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = attn_norm(x[e], den, false);
+      for (int e = 0; e < 4; ++e) a[e] = attn_norm(x[e], den);
     }
     int32_t* o = a_out + ((size_t)t * Mt + r0 + iq) * d + h * DH + n * 16 + 4 * lg;
     if ((reinterpret_cast<uintptr_t>(a_out) & 15) == 0) {  // uniform
@@ -571,7 +561,7 @@ __global__ __launch_bounds__(64 * NMDLM_MAX_T) void k_attn_if(AttnIfArgs a) {
           x = attn_norm4(w.acc[u][n], den);
         } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = attn_norm(w.acc[u][n][e], den, false);
+          for (int e = 0; e < 4; ++e) x[e] = attn_norm(w.acc[u][n][e], den);
         }
         sNum[(t * NT + n) * 64 + lane] = x;
       }
@@ -591,7 +581,7 @@ __global__ __launch_bounds__(64 * NMDLM_MAX_T) void k_attn_if(AttnIfArgs a) {
               cur[k] = attn_norm4(cur[k], den);
             } else {
 #pragma unroll
-              for (int e = 0; e < 4; ++e) cur[k][e] = attn_norm(cur[k][e], den, false);
+              for (int e = 0; e < 4; ++e) cur[k][e] = attn_norm(cur[k][e], den);
             }
           }
         }
