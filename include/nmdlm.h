@@ -164,8 +164,8 @@ size_t nmdlm_qbsm_workspace_size(int T, int M, int K, int N);
  *   NMDLM_BLOCKED_MIN_ROWS active rows of 64 per active word, counted over
  *   the row blocks of the product that read the same words (the whole words
  *   then cost at most twice the active rows' bytes from HBM); else the
- *   row-major rows of W.  Products of many rows (at least 48 to 160 tiles of
- *   128 rows x 256 columns, by K) without bias, per-neuron thresholds or
+ *   row-major rows of W.  Products of many rows (at least 112 to 160 tiles
+ *   of 128 rows x 256 columns, by K) without bias, per-neuron thresholds or
  *   currents beside the spikes take tall tiles, which read every word of the
  *   copy; others of 64-row tiles over at least 1536 output tiles of 64 x 64
  *   (and path 7 in the flags) take wide tiles: four column tiles per

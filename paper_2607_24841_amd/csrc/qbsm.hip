@@ -2132,15 +2132,19 @@ QbsmPlan plan_qbsm(const QbsmCall& c, const QbsmScratch& scr) {
   // the lean product, cold weights: K = 512: 64 workgroups 8.7 / 10.4 us, 128:
   // 11.0 / 10.5; K = 1024: 128: 13.1 / 14.3, 224: 20.8 / 15.7; K = 2048: 128: 16.6 /
   // 23.8, 192: 28.0 / 22.9; K = 8192: 128: 53.6 / 72.1, 256: 134.8 / 73.8.  Against
-  // k_qbsm_words (currents): K = 512: 32: 13.6 / 14.5, 64: 15.6 / 14.6; K = 1024:
-  // 64: 18.6 / 20.3, 112: 25.5 / 21.2; K = 2048: 112: 31.4 / 33.6, 168: 44.0 / 33.7.
+  // k_qbsm_words (currents), counted in tiles of 64 columns, as a last column group
+  // of one tile keeps three waves idle: K up to 512: 192 to 256 tiles 1.10 times its
+  // time, 320 to 384 0.98, 448 to 512 0.96, 640 to 800 0.64; K to 1024: 192 tiles 1.03, 448
+  // to 512 0.90, 512 to 640 0.74; beyond: 512 to 640 0.90, 640 to 800 0.78 (medians of 374
+  // drawn products).
   bool tall = false;
   if (path == 0 && !rt_forced && ((c.flags >> NMDLM_SPLIT_SHIFT) & 0xFFu) <= 1u && tall_fits(c)) {
     const int mbt = 128 / c.T;
     const long long wgs = (long long)((gx + 3) / 4) * ((c.M + mbt - 1) / mbt);
     // (fewer than two row blocks of 128 are mostly padding: 32 x 512 x 32000 8.4 / 11.3,
     // 48 x 1024 x 32000 15.1 / 20.9)
-    tall = R >= 256 && wgs >= (lean ? (Kw <= 8 ? 112 : 160) : (Kw <= 8 ? 48 : (Kw <= 16 ? 112 : 160)));
+    tall = R >= 256 && (lean ? wgs >= (Kw <= 8 ? 112 : 160)
+                             : (long long)gx * ((c.M + mbt - 1) / mbt) >= (Kw <= 16 ? 448 : 640));
   }
   if (tall) {
     lean = wide = false;

@@ -22,7 +22,9 @@ def tall(plans):
 
 
 # T, M, K, N, spikes alone on tall tiles, currents alone on tall tiles: enough
-# workgroups, or just too few (currents: from 48 on at K <= 512)
+# workgroups or tiles, or just too few (currents: 448 tiles of 64 columns at K <= 1024).
+# N of every remainder by four: rows of currents at every alignment, the last store
+# of 1, 2, 3 and 4 of them
 PRODUCTS = [
     (4, 879, 500, 1000, True, True),     # 28 row blocks, the last of 15 tokens; the last tile of 40 columns
     (4, 897, 65, 1030, True, True),      # two words of K; one token in the last row block; tiles past N
@@ -31,11 +33,19 @@ PRODUCTS = [
     (1, 3470, 320, 1000, True, True),    # 128-token row blocks, the last of 14
     (4, 1270, 1000, 1000, True, True),   # 16 words, 160 workgroups
     (4, 512, 2100, 2500, True, True),    # 33 words, 160 workgroups
-    (4, 379, 500, 1000, False, True),    # 48 workgroups: spikes on lean tiles
-    (1, 1530, 320, 1000, False, True),
-    (2, 760, 512, 1024, False, True),
-    (8, 190, 257, 1024, False, True),
-    (4, 350, 512, 1000, False, False),   # 44 workgroups: the other kernels
+    (4, 879, 257, 1001, True, True),
+    (1, 3470, 65, 1003, True, True),
+    (4, 889, 1000, 1000, False, True),   # 112 workgroups: spikes on lean tiles
+    (2, 890, 700, 2047, False, True),
+    (8, 1000, 64, 449, True, True),      # 126 workgroups: four of the last group's columns
+    (4, 4000, 100, 193, True, True),     # 125, the last column alone in its tile
+    (4, 860, 500, 950, False, False),    # 405 tiles: the other kernels
+    (4, 379, 500, 1000, False, False),
+    (1, 1530, 320, 1000, False, False),
+    (2, 760, 512, 1024, False, False),
+    (8, 190, 257, 1024, False, False),
+    (4, 350, 512, 1000, False, False),
+    (8, 1780, 257, 70, True, False),     # 112 workgroups, but two column tiles in each
 ]
 
 
@@ -101,12 +111,13 @@ def test_batched_step(n, C, M, d, H, F, T, on_tall):
     _batched_matches_independent(n, C, M, d, H, F, 0, T, blocked=True)
 
 
-@pytest.mark.parametrize("M,kernel", [(310, "tall"), (157, "lean"), (16, "lean")])
-def test_head_logits(M, kernel):
+@pytest.mark.parametrize("M,V,kernel", [(310, 3008, "tall"), (310, 2992, "tall"), (157, 3008, "lean"),
+                                        (16, 3008, "lean")])
+def test_head_logits(M, V, kernel):
     """10 row blocks x 12 column groups, the last of 22 tokens and three column
-    tiles; and the same head on lean tiles."""
+    tiles, the last of 64 or 48 columns; and the same head on lean tiles."""
     torch, B = need_gpu()
-    m = synth.make_mdlm(5, 1, d=256, H=4, F=256, V=3008, T=4, max_pos=320)
+    m = synth.make_mdlm(5, 1, d=256, H=4, F=256, V=V, T=4, max_pos=320)
     assert plan(4, M, m.d, m.V, mode=HEAD, blocked=1).kernel == kernel
     toks = synth.random_tokens(6, M, m.V).astype(np.int32)
     dm = B.DeviceModel.from_mdlm(m, M, blocked=True)
