@@ -1745,6 +1745,8 @@ constexpr size_t kWordsLdsBudget = 81920;  // word product: two workgroups per C
 constexpr int kWideMinTiles = 1536;  // output tiles (64 x 64) from which blocked products go wide
 constexpr long long kLeanMaxBytes = 1 << 24;  // weights read whole whatever the rows
 constexpr int kLeanTallWgs = 192;    // workgroups of 64-row lean tiles from which 32 rows give way
+constexpr int kLeanShortK = 8;       // words of K below which a lean workgroup has idle waves
+constexpr int kLeanShortWgs = 448;   // and of 64-row tiles of one step from which they pay there
 constexpr int kSplitTiles = 64;      // output tiles up to which, and
 constexpr int kSplitWords = 128;     // words of K from which a product is split over K
 constexpr int kCus = 256;            // compute units of the device
@@ -2083,9 +2085,13 @@ QbsmPlan plan_qbsm(const QbsmCall& c, const QbsmScratch& scr) {
   // tall enough tiles read each weight from L2 fewer times: 64 rows, eight
   // waves, while that leaves most CUs a workgroup (256 x 14336 x 4096 24.8
   // against 32.3 us with 32 rows, 128 x 2048 x 6144 8.6 against 9.3)
-  if (lean && RT == 2 && 64 / c.T >= 1 &&
-      (long long)gx * ((c.M + 64 / c.T - 1) / (64 / c.T)) >= kLeanTallWgs)
-    RT = 4;
+  if (lean && RT == 2) {
+    const long long wgs = (long long)gx * ((c.M + 64 / c.T - 1) / (64 / c.T));
+    // (one step and a short K: four waves integrate 64 tokens a tile and idle before.
+    // 325 x 175 x 3272, 312 workgroups: k_qbsm_words 9.5 us, lean 10.8; from 448 on level)
+    if (c.T == 1 && Kw < kLeanShortK && wgs > kCus && wgs < kLeanShortWgs) lean = false;
+    else if (wgs >= kLeanTallWgs) RT = 4;
+  }
   while (RT > 1 && 16 * RT / 2 >= R && 16 * RT / 2 >= c.T) RT >>= 1;  // no empty tiles
   while (has_tr && RT > 1 && (16 * RT) / c.T > 32) RT >>= 1;  // channel-major: <= 32 tokens
   if (has_tr && c.seq_len > 0) {
@@ -2117,6 +2123,11 @@ QbsmPlan plan_qbsm(const QbsmCall& c, const QbsmScratch& scr) {
     // its grid is one-dimensional, the tile coordinates a float quotient: from
     // kFloatGrid tiles on the other kernels, which divide in integers there
     lean = lean_lds(RT, lean_waves(RT, Kw, gx, c), Kw) <= kDmaLdsMax && wgs < kFloatGrid;
+    // below K = 512 half of its eight waves have no word, and more than two such
+    // workgroups per CU run in two rounds where k_qbsm_words takes four waves
+    // (52 rows x 124 x 10055, 632 workgroups: 6.8 us against 8.5; 296 x 106 x 2841,
+    // 855: 7.3 / 10.0)
+    if (Kw < kLeanShortK && RT <= 2) lean = lean && wgs <= 2 * kCus;
     // a workgroup walks all of K, at 12.5 us for 8192 words' rows of cold weights:
     // where k_qbsm_words splits a long K four ways, up to K = 10240, and to 16384
     // for a matrix of at most 8 MB, which stays in the last-level cache between

@@ -79,7 +79,7 @@ def test_block_step(C, M, d, H, F, T):
 
 @pytest.mark.parametrize("n,C,M,d,H,F,T", [
     (5, 24, 12, 256, 4, 512, 4),    # 12-token sequences: four tokens a row block of the value cache
-    (6, 32, 16, 256, 4, 512, 8),
+    (6, 32, 16, 512, 8, 512, 8),    # (d = 256 runs QKV on the word kernel: 1152 tiles of four words)
 ])
 def test_batched_step(n, C, M, d, H, F, T):
     need_gpu()

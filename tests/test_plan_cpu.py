@@ -73,6 +73,23 @@ def test_lean_rule(T, M, K, N, kernel, splits):
     assert plan(T, M, K, N).kernel != "lean"               # nor without the copy
 
 
+@pytest.mark.parametrize("T,M,K,N,kernel,rows", [
+    (4, 13, 124, 10055, "words", 16),    # 632 workgroups, more than two per CU
+    (8, 37, 106, 2841, "words", 16),
+    (4, 13, 124, 8192, "lean", 16),      # 512
+    (4, 13, 512, 10055, "lean", 32),     # a word for every wave: taller tiles
+    (1, 325, 175, 3272, "words", 32),    # one step, 312 workgroups of 64 rows
+    (1, 256, 175, 4096, "lean", 64),     # 256: one per CU, eight waves
+    (1, 325, 175, 2600, "words", 16),    # 861 of 16
+    (1, 325, 175, 4800, "lean", 64),     # 450
+    (2, 163, 175, 3272, "lean", 64),     # two steps
+])
+def test_lean_with_few_words(T, M, K, N, kernel, rows):
+    """K below 512 leaves lean waves idle: only where the grid fits at once."""
+    p = plan(T, M, K, N, blocked=1)
+    assert (p.status, p.kernel, p.rows) == (B.NMDLM_OK, kernel, rows)
+
+
 def test_attention_route():
     """One kernel or two, and the parts of a timestep."""
     # one timestep: four parts of any context, while they run at once
