@@ -2092,6 +2092,17 @@ QbsmPlan plan_qbsm(const QbsmCall& c, const QbsmScratch& scr) {
     if (c.T == 1 && Kw < kLeanShortK && wgs > kCus && wgs < kLeanShortWgs) lean = false;
     else if (wgs >= kLeanTallWgs) RT = 4;
   }
+  // one 64-row workgroup on a CU (beyond K = 7500, by its LDS): whole rounds of
+  // the chip, and a last row block that is mostly empty costs as much as the others.
+  // 32 rows where those rounds hold a third more than the 32-row tiles do (64 / 32 rows,
+  // k_qbsm_words: 156 x 14677 x 5973, 282 workgroups, 41.3 / 29.1 us, 32.6; 134 x 14024 x
+  // 11963, 561, 63.1 / 48.9, 55.3; below a third 175 x 15560 x 10656, 501, 46.2 / 61.1, 68.0)
+  if (lean && RT == 4 && lean_lds(4, 8, Kw) > kDmaLdsMax / 2 && lean_lds(4, 8, Kw) <= kDmaLdsMax) {
+    const int m4 = 64 / c.T, m2 = 32 / c.T;
+    const long long wgs = (long long)gx * ((c.M + m4 - 1) / m4), rounds = (wgs + kCus - 1) / kCus;
+    // (more tiles are the wide ones')
+    if (wgs < kWideMinTiles && 6 * kCus * rounds >= 4LL * gx * ((c.M + m2 - 1) / m2)) RT = 2;
+  }
   while (RT > 1 && 16 * RT / 2 >= R && 16 * RT / 2 >= c.T) RT >>= 1;  // no empty tiles
   while (has_tr && RT > 1 && (16 * RT) / c.T > 32) RT >>= 1;  // channel-major: <= 32 tokens
   if (has_tr && c.seq_len > 0) {

@@ -35,6 +35,7 @@ SHAPES = [  # T, M, K, N, rows and waves of a tile
     (4, 48, 300, 20000, 64, 4),
     (4, 60, 5000, 4100, 64, 8),     # 64-row tiles of eight waves, K over two staging batches
     (1, 65, 700, 900, 16, 8),       # one step: a row is a token
+    (8, 17, 7600, 5700, 32, 8),     # 32-row tiles of a long K, the last row block of one token
 ]
 
 

@@ -90,6 +90,21 @@ def test_lean_with_few_words(T, M, K, N, kernel, rows):
     assert (p.status, p.kernel, p.rows) == (B.NMDLM_OK, kernel, rows)
 
 
+@pytest.mark.parametrize("T,M,K,N,rows", [
+    (4, 39, 14677, 5973, 32),    # 282 workgroups of 64 rows: two rounds, the third row block half empty
+    (1, 134, 14024, 11963, 32),  # 561: three
+    (8, 17, 7600, 5700, 32),     # 270
+    (8, 17, 7400, 5700, 64),     # two workgroups a CU
+    (7, 25, 15560, 10656, 64),   # 501: two rounds nearly full
+    (4, 64, 14336, 4096, 64),    # 256: one
+    (4, 64, 14336, 4160, 32),    # 260
+])
+def test_lean_rounds(T, M, K, N, rows):
+    """64-row tiles, one workgroup on a CU, only where their rounds are full."""
+    p = plan(T, M, K, N, blocked=1)
+    assert (p.status, p.kernel, p.rows) == (B.NMDLM_OK, "lean", rows)
+
+
 def test_attention_route():
     """One kernel or two, and the parts of a timestep."""
     # one timestep: four parts of any context, while they run at once
