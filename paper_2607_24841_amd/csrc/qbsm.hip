@@ -1932,11 +1932,12 @@ static nmdlm_status launch_lean(const QbsmArgs& a, int tiles, size_t dyn, hipStr
 // Waves of a lean workgroup: as k_qbsm_words for one and two row groups; four
 // row groups take eight where the grid or K is long for four (256 x 4096 x
 // 14336, 896 workgroups: 27.7 against 31.5 us; 128 x 2048 x 32000, 1000: 22.3
-// against 19.2).
+// against 19.2).  From 63 words on LDS holds two such workgroups on a CU, not three
+// (1560 x 4015 x 17418, T = 3: four waves 178.6 us, eight 151.7; k_qbsm_words 155.8).
 static int lean_waves(int RT, int Kw, int gx, const QbsmCall& c) {
   if (RT != 4) return RT == 1 && Kw > 32 ? 16 : 8;
   const int mb = 64 / c.T;
-  return Kw >= 64 || (long long)gx * ((c.M + mb - 1) / mb) <= kCus ? 8 : 4;
+  return Kw >= 63 || (long long)gx * ((c.M + mb - 1) / mb) <= kCus ? 8 : 4;
 }
 // LDS of k_qbsm_lean (mirrors its declarations) and its dynamic part
 static size_t lean_dyn(int RT, int Kw) {
@@ -2134,6 +2135,11 @@ QbsmPlan plan_qbsm(const QbsmCall& c, const QbsmScratch& scr) {
     // its grid is one-dimensional, the tile coordinates a float quotient: from
     // kFloatGrid tiles on the other kernels, which divide in integers there
     lean = lean_lds(RT, lean_waves(RT, Kw, gx, c), Kw) <= kDmaLdsMax && wgs < kFloatGrid;
+    // many 64-row tiles of 65 to 69 words, of steps that the tall and wide tiles don't
+    // take: four workgroups of k_qbsm_words fit a CU's LDS, two of lean (T = 5, 3290 rows
+    // x 4257 x 8506, 7315 workgroups, 168 us against 191; 930 x 4311 x 3734, 944: 29.9 / 30.9;
+    // from 70 words on three fit, 1176 x 4443 x 10994 101 / 98)
+    if (RT == 4 && Kw > 64 && words_lds(4, 4, Kw) <= kDmaLdsMax / 4 && wgs >= 5 * kCus) lean = false;
     // below K = 512 half of its eight waves have no word, and more than two such
     // workgroups per CU run in two rounds where k_qbsm_words takes four waves
     // (52 rows x 124 x 10055, 632 workgroups: 6.8 us against 8.5; 296 x 106 x 2841,

@@ -105,6 +105,20 @@ def test_lean_rounds(T, M, K, N, rows):
     assert (p.status, p.kernel, p.rows) == (B.NMDLM_OK, "lean", rows)
 
 
+@pytest.mark.parametrize("T,M,K,N,kernel,waves", [
+    (5, 658, 4257, 8506, "words", 4),    # 7315 workgroups: four fit a CU, two of the lean ones
+    (7, 612, 4414, 6434, "words", 4),
+    (5, 104, 4257, 8506, "lean", 8),     # 1197
+    (6, 196, 4443, 10994, "lean", 8),    # 70 words: three
+    (7, 206, 4096, 12000, "lean", 8),    # 64 words
+    (7, 36, 3975, 25067, "lean", 8),     # 63: two lean workgroups a CU, of eight waves
+    (7, 36, 3960, 25067, "lean", 4),     # 62: three of four
+])
+def test_lean_residency(T, M, K, N, kernel, waves):
+    p = plan(T, M, K, N, blocked=1)
+    assert (p.status, p.kernel, p.rows, p.waves) == (B.NMDLM_OK, kernel, 64, waves)
+
+
 def test_attention_route():
     """One kernel or two, and the parts of a timestep."""
     # one timestep: four parts of any context, while they run at once
