@@ -2171,8 +2171,13 @@ QbsmPlan plan_qbsm(const QbsmCall& c, const QbsmScratch& scr) {
     const long long wgs = (long long)((gx + 3) / 4) * ((c.M + mbt - 1) / mbt);
     // (fewer than two row blocks of 128 are mostly padding: 32 x 512 x 32000 8.4 / 11.3,
     // 48 x 1024 x 32000 15.1 / 20.9)
-    tall = R >= 256 && (lean ? wgs >= (Kw <= 8 ? 112 : 160)
-                             : (long long)gx * ((c.M + mbt - 1) / mbt) >= (Kw <= 16 ? 448 : 640));
+    // In products of few columns a group of fewer than four tiles leaves waves idle: K
+    // beyond 512 beside the lean product also by tiles of 64 columns (160 workgroups and
+    // more, lean / tall: 5200 x 3000 x 64 in T = 4, 163 tiles 13.5 / 26.2 us; T = 8, 10264 x 3450
+    // x 273, 405 tiles 24.4 / 30.9; 560 to 640 level; K to 1024 320 to 400 tiles 1.1 times)
+    const long long tiles = (long long)gx * ((c.M + mbt - 1) / mbt);
+    tall = R >= 256 && (lean ? wgs >= (Kw <= 8 ? 112 : 160) && tiles >= (Kw <= 8 ? 0 : (Kw <= 16 ? 320 : 640))
+                             : tiles >= (Kw <= 16 ? 448 : 640));
   }
   if (tall) {
     lean = wide = false;

@@ -105,6 +105,19 @@ def test_lean_rounds(T, M, K, N, rows):
     assert (p.status, p.kernel, p.rows) == (B.NMDLM_OK, "lean", rows)
 
 
+@pytest.mark.parametrize("T,M,K,N,kernel", [
+    (4, 5200, 3000, 64, "lean"),      # 163 workgroups of one column tile
+    (8, 1283, 3450, 273, "lean"),     # 162, five column tiles in two groups
+    (8, 1283, 3450, 512, "tall"),     # 162 full ones
+    (4, 5200, 1000, 64, "lean"),
+    (4, 5200, 1000, 128, "tall"),     # 326 tiles
+    (4, 5200, 500, 64, "tall"),
+])
+def test_tall_with_few_columns(T, M, K, N, kernel):
+    p = plan(T, M, K, N, blocked=1)
+    assert (p.status, p.kernel) == (B.NMDLM_OK, kernel)
+
+
 @pytest.mark.parametrize("T,M,K,N,kernel,waves", [
     (5, 658, 4257, 8506, "words", 4),    # 7315 workgroups: four fit a CU, two of the lean ones
     (7, 612, 4414, 6434, "words", 4),
