@@ -179,8 +179,10 @@ struct QbsmArgs {
   int64_t thr_den;
   uint64_t* s_neg_out;
   int64_t* v_out;
-  // word product: 0 = MFMA, 1 = scalar gather-accumulate
-  int accum;
+  union {
+    int accum;               // word product: 0 = MFMA, 1 = scalar gather-accumulate
+    int n_tiles;             // lean product: workgroups without the statistics' one
+  };
   // blocked weights (operand order, see launch_weight_block) or null, and
   // the active rows per active word from which a wave reads them
   const int8_t* Wb;

@@ -1196,7 +1196,7 @@ void k_qbsm_lean(QbsmArgs a) {
     return;
   }
   // row blocks of one column tile, then the next tile, on one XCD
-  const int lid = xcd_order((int)blockIdx.x - extra, (int)gridDim.x - extra);
+  const int lid = xcd_order((int)blockIdx.x - extra, a.n_tiles);
   const int x = __builtin_amdgcn_readfirstlane(div_small(lid, a.inv_gy)), y = lid - x * a.n_rblk;
   const int lds_row = 2 * Kw + 1, items = ROWS * Kw;
 
@@ -2391,6 +2391,7 @@ nmdlm_status launch_qbsm(const QbsmCall& c, const QbsmScratch& scr, hipStream_t 
   if (tall) return launch_tall(a, gx, gy, st, c.ev_begin, c.ev_end);
   if (lean) {
     a.n_rblk = gy;
+    a.n_tiles = tiles;
     return launch_lean_tile(a, tiles, RT, NW, dyn, st, c.ev_begin, c.ev_end);
   }
 
