@@ -376,15 +376,22 @@ __device__ __forceinline__ int keys_of(int jc0, int step, int nch, int J) {
 // grid (H, n_seq * ceil(M/16), T), M queries per sequence, rows of q and
 // a_out sequence-major (n_seq * M per timestep), the caches of sequence s at
 // s * seq_words words past kc / vt.
+//
+// dh = 128 takes 129 registers, one too many for two workgroups on a CU.  WPE = 4
+// (waves per SIMD) holds it to 128, an address pair of the chunk loop spilled: for
+// grids of more workgroups than CUs (T = 8, 133 x 773 keys, 12 heads 28.0 -> 23.2 us; 101 x
+// 899, 16 heads 28.2 -> 23.2); smaller ones lose 4% by the spill.  The
+// entries stand at 1 KB, as the products' do: at 256 bytes the same code took 0.2 us more.
 // ---------------------------------------------------------------------------
-template <int DHW, int NW>
-__global__ __launch_bounds__(NW * 64) void k_attn(const uint64_t* __restrict__ q,
-                                                  const uint64_t* __restrict__ kc,
-                                                  const uint64_t* __restrict__ vt, int64_t cap,
-                                                  int T, int M, int C, int H,
-                                                  const uint8_t* __restrict__ lut,
-                                                  int32_t* __restrict__ a_out, int n_seq,
-                                                  int64_t seq_words) {
+template <int DHW, int NW, int WPE>
+__global__ __launch_bounds__(NW * 64, WPE) __attribute__((aligned(1024)))
+void k_attn(const uint64_t* __restrict__ q,
+            const uint64_t* __restrict__ kc,
+            const uint64_t* __restrict__ vt, int64_t cap,
+            int T, int M, int C, int H,
+            const uint8_t* __restrict__ lut,
+            int32_t* __restrict__ a_out, int n_seq,
+            int64_t seq_words) {
   constexpr int DH = DHW * 64;
   constexpr int NT = DH / 16;
   constexpr int NTH = NW * 64;
@@ -676,7 +683,7 @@ constexpr long long kFusedMinWgs = 128;
 constexpr long long kFullWaves = 2048;  // two waves per SIMD
 // longest walk in one kernel with at most kOneRound workgroups of k_attn:
 // [step][dh / 64 - 1][T = 1, 2 | 3, 4 | 5, 6 | 7, 8] (T = 1, 2: as with parts)
-constexpr long long kOneRound = 256;
+constexpr long long kOneRound = 256;  // one workgroup of k_attn per CU
 constexpr int kWalk[2][2][4] = {{{11, 11, 11, 11}, {11, 11, 6, 6}}, {{11, 11, 5, 5}, {11, 5, 2, 1}}};
 
 AttnRoute attn_route(const AttnCall& c) {
@@ -708,9 +715,11 @@ static nmdlm_status launch_attention_dh(const AttnCall& c, hipStream_t st) {
   if (r.groups == 2) return attn_if_launch<DHW, 2>(a, st);
   if (!r.split) return r.parts > 1 ? attn_if_launch<DHW, 1, true>(a, st) : attn_if_launch<DHW, 1>(a, st);
   int32_t* const cur = c.a_out ? c.a_out : c.a_scratch;
-  hipLaunchKernelGGL((k_attn<DHW, kAttnNW>), dim3(c.H, c.n_seq * ((c.M + 15) / 16), c.T),
-                     dim3(kAttnNW * 64), 0, st, c.q, c.k_cache, c.vt_cache, c.cap, c.T, c.M, c.C, c.H,
-                     c.lut, cur, c.n_seq, c.seq_words);
+  const dim3 grid(c.H, c.n_seq * ((c.M + 15) / 16), c.T);
+  const auto fn = (long long)grid.x * grid.y * grid.z > kOneRound ? k_attn<DHW, kAttnNW, DHW == 2 ? 4 : 1>
+                                                                  : k_attn<DHW, kAttnNW, 1>;
+  hipLaunchKernelGGL(fn, grid, dim3(kAttnNW * 64), 0, st, c.q, c.k_cache, c.vt_cache, c.cap, c.T, c.M, c.C,
+                     c.H, c.lut, cur, c.n_seq, c.seq_words);
   const nmdlm_status rc = hip_status();
   if (rc != NMDLM_OK || !c.s_out) return rc;
   return launch_if(cur, c.T, c.n_seq * c.M, c.H * c.dh, c.theta, nullptr, nullptr, nullptr, c.s_out,

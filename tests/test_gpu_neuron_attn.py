@@ -214,6 +214,8 @@ ATTN_ROUTES = [  # T, M, C, H, dh; query groups, parts, kernels apart
     (7, 3, 420, 2, 128, 1, 1, True),
     (4, 15, 750, 3, 128, 1, 2, False),     # twelve chunks over two parts
     (4, 15, 760, 3, 128, 1, 2, True),      # thirteen chunks: the kernels apart
+    (5, 100, 700, 9, 128, 1, 1, True),     # 315 workgroups: two on a CU
+    (5, 100, 700, 7, 128, 1, 1, True),     # 245
     (8, 1000, 64600, 1, 64, 1, 1, True),   # 65600 keys: the 64-bit quotient
     (1, 128, 65500, 16, 64, 1, 4, False),  # and in one kernel, with parts
     (5, 128, 65500, 16, 64, 1, 1, False),  # and without
