@@ -9,8 +9,8 @@ context prefill runs once, untimed.  Weights are seeded int8 uniforms
 (workloads/synth.py); 640 MB of weights per step, more than the 256 MB
 last-level cache, so every step streams its weights from HBM.  The model
 also holds the blocked copies of its weights (--weights blocked, the
-default): each wave of a product reads them when its words' union is dense;
---weights rows keeps the row-major weights only.
+default), of which its products read every word; --weights rows keeps the
+row-major weights only, of which they read the rows active in the block.
 
 A "step" is one nmdlm_block_step (block input, per layer the QKV product,
 attention, O, up and down products with their neurons, then the head,
@@ -19,8 +19,10 @@ block to fully masked so that every step is the same workload.  One step is
 captured as a HIP graph before the timed region; the timed region replays it
 --steps times after --warmup replays.
 
-Prints one JSON line: block-denoise tokens/s, the weight-skip fraction, the
-touched-weight bandwidth of the whole step, the roofline of the product
+Prints one JSON line: block-denoise tokens/s, the weight-skip fraction and the
+touched-weight bandwidth of the whole step (both by the active rows of the
+block unions, Eq. (13), which is what the algorithm needs and not what a kernel
+over the blocked copies reads: weight_bytes_read_per_step), the roofline of the product
 kernel (every product launch of one step timed with HIP events stamped by
 its own dispatch), and the CPU oracle's rate on a bounded sample.
 
@@ -43,7 +45,7 @@ Other workloads (--workload):
      {1, 4, 16} tokens and K in {1, 2, 4} quantisation levels.
   block-batch      the block step over n_seq in {1, 2, 4, 8, 16, 32, 64, 128}
      sequences at once (each with its own 512-token context and 16-token block): every product
-     reads a weight row once for the whole batch; tokens/s, union fractions and
+     needs a weight row once for the whole batch; tokens/s, union fractions and
      touched bytes per point, beside the analytic model at the measured unions.
 """
 from __future__ import annotations
@@ -381,6 +383,14 @@ def cpu_info():
     return model, os.cpu_count() or 1
 
 
+def copy_bytes(stats):
+    """Weight bytes of products that read every word of their blocked copies
+    (each once, from HBM; row blocks that share a word find it in a cache):
+    64-row words of 64-column tiles.  Every product of the 12-layer step and of
+    the one-block step is such a one."""
+    return int(((stats[:, 0] + 63) // 64 * ((stats[:, 2] + 63) // 64) * 4096).sum())
+
+
 def blas_threads():
     try:
         from threadpoolctl import threadpool_info
@@ -561,6 +571,7 @@ def bench_mdlm12_step(args):
         "weight_skip_fraction": 1.0 - touched / dense,
         "touched_weight_bytes_per_step": touched,
         "touched_weight_GBps": touched / (ms_per_step * 1e-3) / 1e9,
+        "weight_bytes_read_per_step": copy_bytes(st) if args.weights == "blocked" else touched,
         "roofline": {"kernel": ("k_qbsm_lean" if args.weights == "blocked" else "k_qbsm_words") +
                                " (int8 MFMA spike product with fused epilogue; all "
                                "49 product launches of the step)",
@@ -1136,6 +1147,7 @@ def bench_block(args):
         "weight_skip_fraction": skip,
         "touched_weight_bytes_per_step": w_touched,
         "touched_weight_GBps": w_touched / (ms_per_step * 1e-3) / 1e9,
+        "weight_bytes_read_per_step": copy_bytes(st) if args.weights == "blocked" else w_touched,
         "roofline": {
             "kernel": "k_qbsm (int8 MFMA spike product with fused IF epilogue)",
             "bound": "hbm",

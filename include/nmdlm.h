@@ -18,7 +18,7 @@
  * Padding bits must be zero on input and are written as zero on output.
  *
  * Weight matrices are int8 [K][ldw] row-major: row k holds the weights that
- * leave input neuron k (its fan-out), so the products below skip whole rows.
+ * leave input neuron k (its fan-out), so a product can skip whole rows.
  * ldw is a multiple of 16 and >= N; bytes [N, ldw) of a row may be read and
  * are ignored.  K * ldw must be below 2^31.
  */
@@ -85,13 +85,16 @@ typedef enum nmdlm_status {
 
 /*
  * Statistics of one spike product, written by the device (int64 so the
- * host can sum them).  weight_bytes is the number of weight bytes the
- * product reads: k_active * n (the per-block load of Eq. (13)).
+ * host can sum them).  They count the block's union, whichever kernel ran:
+ * weight_bytes = k_active * n is the per-block load of Eq. (13), the bytes of
+ * the active rows.  The kernels over row-major weights read those; the lean,
+ * tall and wide products over a blocked copy read more, up to every row (see
+ * nmdlm_qbsm_blocked), and NMDLM_FORCE_DENSE counts every row.
  */
 typedef struct nmdlm_qbsm_stats {
   int64_t k_total;       /* K                                             */
   int64_t k_active;      /* input neurons that spike at least once in the
-                            block (rows of W that are read)               */
+                            block (active rows of W)                      */
   int64_t n;             /* N                                             */
   int64_t weight_bytes;  /* k_active * n                                  */
 } nmdlm_qbsm_stats;
@@ -101,8 +104,9 @@ typedef struct nmdlm_qbsm_stats {
  *
  * Sec. IV-A: the linear operation over the B*T rows of a block,
  *     I[t,m,n] = bias[n] + sum_k S[t,m,k] * W[k,n],
- * where, by assumption (ii), row k of W is read only if input neuron k
- * spikes at least once among all T*M rows.  The result is identical to the
+ * where, by assumption (ii), row k of W is needed only if input neuron k
+ * spikes at least once among all T*M rows, and only then read here (a row
+ * block of the product reads the rows active in it).  The result is identical to the
  * dense product (integer arithmetic, no overflow for K*127 + |bias| < 2^31).
  *
  * Optional fused integrate-and-fire epilogue (Sec. II-B, Eqs. (3)-(4),
@@ -140,13 +144,11 @@ size_t nmdlm_qbsm_workspace_size(int T, int M, int K, int N);
  * dense and the products are plain int8 contractions.
  *
  * Sec. IV-A (Eqs. (12)-(13)): the row-load rule reads row k of W only if
- * input neuron k spikes in the block.  Over the blocked copy the rule is
- * applied per 64-row word: a word with no active row is skipped, every row
- * of an active word is read (rows that do not spike meet zero inputs, so the
- * result is unchanged).  At dense unions the bytes read are those of the
- * row-major path; the copy's bytes sit in MFMA operand order, so a 64-row
- * word of a 64-column tile is four 16-byte loads per lane with no byte
- * transposes.
+ * input neuron k spikes in the block.  Over the blocked copy whole 64-row
+ * words are read: rows that do not spike meet zero inputs, so the result is
+ * unchanged, and at dense unions the bytes are those of the row-major path.
+ * The copy's bytes sit in MFMA operand order, so a 64-row word of a 64-column
+ * tile is four 16-byte loads per lane with no byte transposes.
  *
  * Layout: for word w (rows 64w..64w+63) and column tile x (columns
  * 64x..64x+63), 4096 bytes at offset (w * ceil(N/64) + x) * 4096; within
@@ -158,19 +160,25 @@ size_t nmdlm_qbsm_workspace_size(int T, int M, int K, int N);
  *   nmdlm_weight_blocked_bytes) from W (as for nmdlm_qbsm); asynchronous on
  *   the stream.  The copy must be rebuilt whenever W changes.
  * nmdlm_qbsm_blocked: nmdlm_qbsm (same arguments, results and errors) with
- *   the blocked copy Wb of W also given.  With path 6 in the flags every
- *   word is read from the copy; unforced, each wave of the product reads it
- *   when its words' union is dense: on average at least
- *   NMDLM_BLOCKED_MIN_ROWS active rows of 64 per active word, counted over
- *   the row blocks of the product that read the same words (the whole words
- *   then cost at most twice the active rows' bytes from HBM); else the
- *   row-major rows of W.  Products of many rows (at least 112 to 160 tiles
- *   of 128 rows x 256 columns, by K) without bias, per-neuron thresholds or
- *   currents beside the spikes take tall tiles, which read every word of the
- *   copy; others of 64-row tiles over at least 1536 output tiles of 64 x 64
- *   (and path 7 in the flags) take wide tiles: four column tiles per
- *   workgroup, each read from the copy over all of K.  Results do not depend
- *   on which is used.
+ *   the blocked copy Wb of W also given.  Unforced, the sizes and options
+ *   choose among
+ *   - lean: products with neurons or a head, without bias, per-neuron
+ *     thresholds or currents, of at least 64 rows T*M or a matrix of at most
+ *     16 MB (less where K is below 512 or long, by measured lines).  Every
+ *     word of the copy is read, also one without an active row: the loads do
+ *     not wait for the union;
+ *   - tall: such products, or currents alone, of many rows (at least 112 to
+ *     160 tiles of 128 rows x 256 columns, by K).  Every word is read;
+ *   - wide: others of 64-row tiles over at least 1536 output tiles of 64 x
+ *     64 (and path 7 in the flags): four column tiles per workgroup; every
+ *     word with an active row of the row block is read;
+ *   - the others read a word without an active row not at all, and each wave
+ *     takes the words from the copy when their union is dense: on average at
+ *     least NMDLM_BLOCKED_MIN_ROWS active rows of 64 per active word, counted
+ *     over the row blocks of the product that read the same words (the whole
+ *     words then cost at most twice the active rows' bytes from HBM); else
+ *     the row-major rows of W.  Path 6 in the flags: always from the copy.
+ *   Results and statistics do not depend on which is used.
  *   NMDLM_ERR_UNSUPPORTED when the copy would exceed 2^31 bytes.
  * ------------------------------------------------------------------------ */
 #define NMDLM_BLOCKED_MIN_ROWS 32
@@ -396,7 +404,7 @@ size_t nmdlm_bbm_attn_workspace_size(int T, int M, int H, int dh);
  *
  * Several sequences in one step (io->n_seq > 1): n_seq independent
  * sequences at the same block (same M, C, pos0) share every product, so a
- * weight row is read once when it is active for any of their n_seq*M tokens
+ * weight row counts once when it is active for any of their n_seq*M tokens
  * (the row-load rule of Sec. IV over the batch); attention, the caches and
  * the unmasking stay per sequence.  Token-indexed buffers then hold the
  * sequences one after the other: tokens/masked/pred/conf [n_seq][M], spikes
@@ -425,9 +433,8 @@ typedef struct nmdlm_layer {
   uint64_t* vt_cache;    /* device [T][cache_cap/64][d]: bit j%64 of word
                             (t, j/64, c) is value channel c of position j */
   /* Blocked copies (nmdlm_weight_block, ldw = N) of the four weights, or
-   * NULL.  With a copy, each wave of a product reads it when its words'
-   * union, counted over the row blocks that share the words, is dense
-   * (NMDLM_BLOCKED_MIN_ROWS), else the row-major rows.  Path 6 in the flags
+   * NULL.  With a copy, the products choose as nmdlm_qbsm_blocked does (of 64
+   * rows T*M and more, most read every word of it).  Path 6 in the flags
    * (every word from the copies) requires every copy, and the head's when
    * the step runs the head (NMDLM_ERR_INVALID_ARG otherwise).  Results do
    * not depend on it. */
