@@ -72,8 +72,9 @@ __device__ __forceinline__ v4i attn_norm4(v4i num, int den_i) {
 // Per 32 queries and chunk (QG = 2, dh = 128) that is 125 vector instructions
 // and 32 MFMAs, where scoring by popcounts took 350 vector instructions per 16
 // queries; the key and value expansions (100 of the 125) are shared by the QG
-// query groups.  Bound by LDS (140 clocks of a CU per chunk, 64 of them the 32
-// table reads) and by instruction issue (620 clocks of a SIMD), about equally.
+// query groups.  Bound by LDS, whose indexed path is busy 51% of the cycles (a third of
+// that conflicts of the table reads, 32 of them a chunk), and by instruction issue;
+// the matrix cores are busy 37% (counters of the call below).
 // T = 4, 16 heads of 128, 2048 queries x 2048 keys: 213 -> 76 us (1.8 POP/s).
 // ---------------------------------------------------------------------------
 typedef uint32_t __attribute__((may_alias)) u32_alias;

@@ -249,8 +249,10 @@ __device__ __forceinline__ void tall_epilogue(const QbsmArgs& a, const v4i (&acc
 // of two words of one row, a piece per half word of products.  Every word is
 // read and multiplied: over 128 rows a word of 64 channels has its spike.
 //
-// Bound by the matrix cores in the loop (about 75% busy) and by the chain of
-// loads before it and the neurons after it, some 8 us a round of the chip.
+// Bound by the matrix cores in the loop and by the chain of loads before it and the
+// neurons after it, some 8 us a round of the chip: over the whole kernel the matrix
+// cores are busy 50-57% of the cycles of a prefill's products (K = 2048 and 8192), 31-37%
+// at K = 1024 (counters).
 // Rows x K x N, T = 4, against 64-row tiles: 8192 x 2048 x 6144 118 -> 80 us
 // (2.6 POP/s), 8192 x 8192 x 2048 253 -> 96 (2.9), 8192 x 1024 x 3072 40 -> 29,
 // 2048 x 1024 x 4096 20.7 -> 14.1; T = 8, 5552 x 1024 x 3072 52 -> 29.
