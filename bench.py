@@ -93,10 +93,10 @@ def parse():
 # A value holds only for the product-kernel sources with the recorded digest:
 # any change to them reports null until the counters are taken again.
 TRAFFIC = {
-    "block": {"sources_sha256": "fc86da0ff2f80f4b93457c5fe8375e7be50dccbc03ec8dba1b5897440c3dd954",
-              "bytes_per_launch": 2773553.6},
-    "mdlm12": {"sources_sha256": "fc86da0ff2f80f4b93457c5fe8375e7be50dccbc03ec8dba1b5897440c3dd954",
-               "bytes_per_launch": 14211689.4},
+    "block": {"sources_sha256": "a64927f2ca6888a4c2503d17945cfeccf5c3a5abf9c1e3263534bc08fd967630",
+              "bytes_per_launch": 3648167.2},
+    "mdlm12": {"sources_sha256": "a64927f2ca6888a4c2503d17945cfeccf5c3a5abf9c1e3263534bc08fd967630",
+               "bytes_per_launch": 14649513.1},
 }
 PRODUCT_SOURCES = ("paper_2607_24841_amd/csrc/qbsm.hip", "paper_2607_24841_amd/csrc/qbsm_device.h",
                    "paper_2607_24841_amd/csrc/tall.hip", "paper_2607_24841_amd/csrc/common.h")
